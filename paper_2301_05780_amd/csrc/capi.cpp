@@ -329,8 +329,15 @@ pdd_status get_spec(pdd_ctx* ctx, int32_t p, SpecCache** out) {
       all.resize(off + len, 0.0);
       return off;
     };
-    const size_t o_nodes = put(t.nodes, SPEC_T), o_bw = put(t.bw, SPEC_T), o_D = put(t.D, nn),
-                 o_D2b = put(t.D2b, 2 * SPEC_T), o_V = put(t.V, nn), o_Vi = put(t.Vinv, nn), o_lam = put(t.lam, SPEC_T);
+    auto frag = [&](const std::vector<double>& v) {
+      std::vector<double> f(nn);
+      for (int i = 0; i < SPEC_T; ++i)
+        for (int k = 0; k < SPEC_T; ++k) f[spec_frag(i, k)] = v[(size_t)i * SPEC_T + k];
+      return f;
+    };
+    const size_t o_nodes = put(t.nodes, SPEC_T), o_bw = put(t.bw, SPEC_T), o_D = put(frag(t.D), nn),
+                 o_D2b = put(t.D2b, 2 * SPEC_T), o_V = put(frag(t.V), nn), o_Vi = put(frag(t.Vinv), nn),
+                 o_lam = put(t.lam, SPEC_T);
     hipError_t e = fresh->buf.reserve(all.size() * sizeof(double));
     if (e != hipSuccess) return check_hip(ctx, e, "hipMalloc(spectral tables)");
     if ((e = hipMemcpy(fresh->buf.ptr, all.data(), all.size() * sizeof(double), hipMemcpyHostToDevice)) != hipSuccess)
@@ -441,7 +448,7 @@ pdd_status pdd_spectral_eval(pdd_ctx* ctx, const pdd_partition* part, int32_t p,
   pdd_status st = get_spec(ctx, p, &sc);
   if (st != PDD_OK) return st;
   return check_hip(ctx, launch_spectral_eval(sc->dev, p, part->H, part->x0, part->x1, part->y0, part->y1, grid, n_pts,
-                                             xy, 0, u, grad, nullptr, ctx->stream),
+                                             xy, u, grad, ctx->stream),
                    "launch spectral eval");
 }
 
@@ -456,8 +463,8 @@ pdd_status pdd_spectral_grad_lut(pdd_ctx* ctx, const pdd_partition* part, int32_
   SpecCache* sc = nullptr;
   pdd_status st = get_spec(ctx, p, &sc);
   if (st != PDD_OK) return st;
-  return check_hip(ctx, launch_spectral_eval(sc->dev, p, part->H, part->x0, part->x1, part->y0, part->y1, grid, 0,
-                                             nullptr, lut_n, nullptr, nullptr, grad_lut, ctx->stream),
+  return check_hip(ctx, launch_spectral_table(sc->dev, p, part->H, part->x0, part->x1, part->y0, part->y1, grid, lut_n,
+                                              grad_lut, ctx->stream),
                    "launch spectral grad table");
 }
 

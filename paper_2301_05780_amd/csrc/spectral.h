@@ -31,7 +31,12 @@ struct SpectralTables {
 
 bool spectral_tables(int32_t p, SpectralTables& t, std::string& err);
 
-// Device copies of the tables of one p.
+// Position of entry (i, k) of a 64 x 64 table in the order in which the waves
+// of the dense products load it: sixteen rows, then K step, then lane (row
+// i % 16 and k % 4 of the step).
+inline size_t spec_frag(int i, int k) { return (size_t)(i / 16) * 1024 + (k / 4) * 64 + (k % 4) * 16 + i % 16; }
+
+// Device copies of the tables of one p; D, V and Vinv in spec_frag order.
 struct SpecDev {
   const double* nodes;
   const double* bw;
@@ -60,8 +65,10 @@ struct SpecArgs {
 
 hipError_t launch_spectral_solve(const SpecArgs& A, hipStream_t stream);
 hipError_t launch_spectral_eval(const SpecDev& T, int32_t p, int32_t H, double x0, double x1, double y0, double y1,
-                                const double* grid, int64_t n_pts, const double* xy, int32_t lut_n, double* u,
-                                double* grad, float* grad_lut, hipStream_t stream);
+                                const double* grid, int64_t n_pts, const double* xy, double* u, double* grad,
+                                hipStream_t stream);
+hipError_t launch_spectral_table(const SpecDev& T, int32_t p, int32_t H, double x0, double x1, double y0, double y1,
+                                 const double* grid, int32_t lut_n, float* grad_lut, hipStream_t stream);
 hipError_t launch_lut_field_range(const float* lut, int64_t nodes, double* out, hipStream_t stream);
 
 }  // namespace pdd

@@ -12,8 +12,8 @@
 // applied to the side values.  With E = V diag(lam) V^{-1} (host, once per
 // p) the solve is four dense products and a pointwise division:
 //   U = V [(V^{-1} F V^{-T}) / (ax lam_i + ay lam_j + c)] V^T,
-// run per square by one workgroup on the float64 matrix cores
-// (v_mfma_f64_16x16x4_f64) with 64 x 64 tiles in LDS.  Two more products
+// run per square by one workgroup of sixteen waves on the float64 matrix
+// cores (v_mfma_f64_16x16x4_f64) with 64 x 64 tiles in LDS.  Two more products
 // give the grid derivatives (2/S) D U and U ((2/S) D)^T.
 //
 // Grid layout (device, float64): grid[s][f][i][j], square s = a + H c (a
@@ -50,13 +50,34 @@ __device__ __forceinline__ double lattice_value(const SpecArgs& A, bool vert, in
   return A.u_knots[P.lattice[(size_t)iy * (P.L + 1) + ix]];
 }
 
-// Side values: one wave per (square, side); side o = 0 (S), 1 (N), 2 (W),
+// Side values and the source, one launch.  The first `side_blocks`
+// workgroups: one wave per (square, side); side o = 0 (S), 1 (N), 2 (W),
 // 3 (E).  The horizontal sides take all p + 1 points (the corners included),
-// the vertical sides the p - 1 interior ones.
+// the vertical sides the p - 1 interior ones.  The other workgroups: one
+// thread per interior point, whose source value waits in the grid's u field
+// for k_spec_solve.  The source is float64 transcendentals (EQ43: four
+// sincos and a tanh per point, 384,400 points for 100 squares at p = 63) and
+// would keep the solve's few workgroups busy for two thirds of their time;
+// here every CU takes part (17 us for both, the sides alone 8 us).
 template <int KIND>
-__global__ __launch_bounds__(256) void k_spec_sides(SpecArgs A, int32_t smax) {
+__global__ __launch_bounds__(256) void k_spec_sides(SpecArgs A, int32_t smax, int32_t side_blocks) {
   extern __shared__ double sv[];
   const AsmParams& P = A.P;
+  if ((int)blockIdx.x >= side_blocks) {
+    const int n = A.p - 1;
+    const int64_t q = (int64_t)((int)blockIdx.x - side_blocks) * 256 + threadIdx.x;
+    if (q >= (int64_t)A.H * A.H * n * n) return;
+    const int j = (int)(q % n), i = (int)((q / n) % n);
+    const int64_t sq = q / ((int64_t)n * n);
+    const int a = (int)(sq % A.H), c = (int)(sq / A.H);
+    const double Sx = (P.x1 - P.x0) / A.H, Sy = (P.y1 - P.y0) / A.H;
+    const double x = P.x0 + a * Sx + Sx * (A.T.nodes[i + 1] + 1.0) * 0.5;
+    const double y = P.y0 + c * Sy + Sy * (A.T.nodes[j + 1] + 1.0) * 0.5;
+    Coef<double> cf;
+    coef_at<KIND>(P.coef, x, y, cf);
+    gfield(A, sq, 0)[(size_t)(i + 1) * (A.p + 1) + j + 1] = cf.f;
+    return;
+  }
   const int lane = threadIdx.x & 63;
   const int64_t w = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (w >= 4LL * A.H * A.H) return;
@@ -121,88 +142,112 @@ __global__ __launch_bounds__(256) void k_spec_sides(SpecArgs A, int32_t smax) {
   }
 }
 
-// C strip of wave w (rows 16 w .. 16 w + 15) of C = A B for 64 x 64
-// operands: acc[ct] holds the 16 x 16 tile of columns 16 ct .. 16 ct + 15.
-// Operands per lane l and K step: A[16 w + l % 16][k0 + l / 16] and
-// B[k0 + l / 16][16 ct + l % 16]; the float64 accumulator holds element q of
-// lane l at row 16 w + l / 16 + 4 q, column 16 ct + l % 16.
-template <class FA, class FB>
-__device__ __forceinline__ void mfma_strip(FA fa, FB fb, v4d acc[4]) {
+// The 16 x 16 tile of C = A B (64 x 64 operands) that wave w of 16 owns: rows
+// 16 (w / 4) .., columns 16 (w % 4) ...  Operands per lane l and K step:
+// A[row0 + l % 16][k0 + l / 16] and B[k0 + l / 16][col0 + l % 16]; the float64
+// accumulator holds element q of lane l at row row0 + l / 16 + 4 q, column
+// col0 + l % 16.
+constexpr int SOLVE_WAVES = 16;
+
+struct Tile {
+  int row0, col0, r, kq;
+};
+__device__ __forceinline__ Tile my_tile() {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int r = lane & 15, kq = lane >> 4;
+  return Tile{16 * (w >> 2), 16 * (w & 3), lane & 15, lane >> 4};
+}
+
+// The lane's sixteen K-step values T[row0 + l % 16][4 s + l / 16] of a 64 x 64
+// table: the A operand of T X, or the B operand of X T^T.  The tables are
+// stored in this order (spec_frag), so a wave's loads are 512 contiguous
+// bytes each; from row-major tables every load touched 16 lines.
+__device__ __forceinline__ void load_frag(const double* __restrict__ T, int row0, double (&f)[16]) {
+  const double* src = T + row0 * SPEC_T + (threadIdx.x & 63);
 #pragma unroll
-  for (int ct = 0; ct < 4; ++ct) acc[ct] = v4d{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
-  for (int k0 = 0; k0 < SPEC_T; k0 += 4) {
-    const double av = fa(16 * w + r, k0 + kq);
+  for (int s = 0; s < 16; ++s) f[s] = src[64 * s];
+}
+
+// T X: the table's fragment from registers, X from LDS
+__device__ __forceinline__ v4d tile_left(const double (&f)[16], const double* X, const Tile& t) {
+  v4d acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int ct = 0; ct < 4; ++ct)
-      acc[ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, fb(k0 + kq, 16 * ct + r), acc[ct], 0, 0, 0);
-  }
+  for (int s = 0; s < 16; ++s)
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(f[s], X[(4 * s + t.kq) * LDT + t.col0 + t.r], acc, 0, 0, 0);
+  return acc;
+}
+
+// X T^T
+__device__ __forceinline__ v4d tile_right(const double* X, const double (&f)[16], const Tile& t) {
+  v4d acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int s = 0; s < 16; ++s)
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(X[(t.row0 + t.r) * LDT + 4 * s + t.kq], f[s], acc, 0, 0, 0);
+  return acc;
 }
 
 template <class F>
-__device__ __forceinline__ void strip_for_each(const v4d acc[4], F f) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+__device__ __forceinline__ void tile_for_each(const v4d& acc, const Tile& t, F f) {
 #pragma unroll
-  for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) f(16 * w + (lane >> 4) + 4 * q, 16 * ct + (lane & 15), acc[ct][q]);
+  for (int q = 0; q < 4; ++q) f(t.row0 + t.kq + 4 * q, t.col0 + t.r, acc[q]);
 }
 
-// Interior solve and grid derivatives of one square per workgroup (4 waves).
-template <int KIND>
-__global__ __launch_bounds__(256) void k_spec_solve(SpecArgs A) {
+// Interior solve and grid derivatives of one square per workgroup.  Bound by
+// latency (a partition has tens to a few hundred squares and each is a chain
+// of six products), so sixteen waves share the 64 x 64 tiles, one 16 x 16
+// tile per wave and product, and every product's table fragment is loaded
+// while the previous product runs.  100 squares at p = 63 take 30 us (four
+// waves with a 16-row strip each and the source evaluated here: 72 us; the
+// same sixteen waves with row-major tables: 55 us).
+__global__ __launch_bounds__(64 * SOLVE_WAVES) void k_spec_solve(SpecArgs A) {
   __shared__ double B[SPEC_T * LDT];
   const AsmParams& P = A.P;
   const int64_t s = blockIdx.x;
-  const int a = (int)(s % A.H), c = (int)(s / A.H);
   const int p = A.p, N = p + 1, n = p - 1;
   const double Sx = (P.x1 - P.x0) / A.H, Sy = (P.y1 - P.y0) / A.H;
-  const double xa = P.x0 + a * Sx, ya = P.y0 + c * Sy;
   double* U = gfield(A, s, 0);
-  const double* nodes = A.T.nodes;
   const double* D2b = A.T.D2b;
+  const Tile t = my_tile();
   // F: source at the interior points minus the boundary columns of the operator
   for (int e = threadIdx.x; e < SPEC_T * SPEC_T; e += blockDim.x) {
     const int i = e / SPEC_T, j = e % SPEC_T;
     double f = 0.0;
     if (i < n && j < n) {
-      const double x = xa + Sx * (nodes[i + 1] + 1.0) * 0.5;
-      const double y = ya + Sy * (nodes[j + 1] + 1.0) * 0.5;
-      Coef<double> cf;
-      coef_at<KIND>(P.coef, x, y, cf);
-      f = cf.f - A.ax * (D2b[2 * i] * U[(size_t)0 * N + j + 1] + D2b[2 * i + 1] * U[(size_t)p * N + j + 1]) -
+      f = U[(size_t)(i + 1) * N + j + 1] - A.ax * (D2b[2 * i] * U[(size_t)0 * N + j + 1] + D2b[2 * i + 1] * U[(size_t)p * N + j + 1]) -
           A.ay * (D2b[2 * j] * U[(size_t)(i + 1) * N] + D2b[2 * j + 1] * U[(size_t)(i + 1) * N + p]);
     }
     B[i * LDT + j] = f;
   }
+  auto put = [&](const v4d& acc) __attribute__((always_inline)) {
+    __syncthreads();                 // every wave has read the previous tile
+    tile_for_each(acc, t, [&](int i, int j, double v) { B[i * LDT + j] = v; });
+    __syncthreads();
+  };
+  double f0[16], f1[16];
+  load_frag(A.T.Vinv, t.row0, f0);
   __syncthreads();
-  const double* V = A.T.V;
-  const double* Vi = A.T.Vinv;
-  v4d acc[4];
-  auto lds = [&](int i, int k) { return B[i * LDT + k]; };
+  v4d acc;
   // V^{-1} F
-  mfma_strip([&](int i, int k) { return Vi[i * SPEC_T + k]; }, lds, acc);
-  __syncthreads();
-  strip_for_each(acc, [&](int i, int j, double v) { B[i * LDT + j] = v; });
-  __syncthreads();
+  load_frag(A.T.Vinv, t.col0, f1);
+  acc = tile_left(f0, B, t);
+  put(acc);
   // (V^{-1} F) V^{-T}, divided by ax lam_i + ay lam_j + c
-  mfma_strip(lds, [&](int k, int j) { return Vi[j * SPEC_T + k]; }, acc);
-  __syncthreads();
+  load_frag(A.T.V, t.row0, f0);
+  acc = tile_right(B, f1, t);
   const double* lam = A.T.lam;
-  strip_for_each(acc, [&](int i, int j, double v) { B[i * LDT + j] = v / (A.ax * lam[i] + A.ay * lam[j] + A.c); });
-  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) acc[q] = acc[q] / (A.ax * lam[t.row0 + t.kq + 4 * q] + A.ay * lam[t.col0 + t.r] + A.c);
+  put(acc);
   // V (.)
-  mfma_strip([&](int i, int k) { return V[i * SPEC_T + k]; }, lds, acc);
-  __syncthreads();
-  strip_for_each(acc, [&](int i, int j, double v) { B[i * LDT + j] = v; });
-  __syncthreads();
+  load_frag(A.T.V, t.col0, f1);
+  acc = tile_left(f0, B, t);
+  put(acc);
   // (.) V^T: the interior values
-  mfma_strip(lds, [&](int k, int j) { return V[j * SPEC_T + k]; }, acc);
+  load_frag(A.T.D, t.row0, f0);
+  acc = tile_right(B, f1, t);
+  load_frag(A.T.D, t.col0, f1);
   __syncthreads();
   // the whole grid into LDS (zero-padded): interior from the product, sides from global
-  strip_for_each(acc, [&](int i, int j, double v) {
+  tile_for_each(acc, t, [&](int i, int j, double v) {
     if (i < n && j < n) {
       B[(i + 1) * LDT + j + 1] = v;
       U[(size_t)(i + 1) * N + j + 1] = v;
@@ -214,18 +259,17 @@ __global__ __launch_bounds__(256) void k_spec_solve(SpecArgs A) {
     else if (i == 0 || i == p || j == 0 || j == p) B[i * LDT + j] = U[(size_t)i * N + j];
   }
   __syncthreads();
-  const double* Dm = A.T.D;
   const double sx = 2.0 / Sx, sy = 2.0 / Sy;
   double* Gx = gfield(A, s, 1);
   double* Gy = gfield(A, s, 2);
   // du/dx = (2/S) D U
-  mfma_strip([&](int i, int k) { return Dm[i * SPEC_T + k]; }, lds, acc);
-  strip_for_each(acc, [&](int i, int j, double v) {
+  acc = tile_left(f0, B, t);
+  tile_for_each(acc, t, [&](int i, int j, double v) {
     if (i < N && j < N) Gx[(size_t)i * N + j] = sx * v;
   });
   // du/dy = U ((2/S) D)^T
-  mfma_strip(lds, [&](int k, int j) { return Dm[j * SPEC_T + k]; }, acc);
-  strip_for_each(acc, [&](int i, int j, double v) {
+  acc = tile_right(B, f1, t);
+  tile_for_each(acc, t, [&](int i, int j, double v) {
     if (i < N && j < N) Gy[(size_t)i * N + j] = sy * v;
   });
 }
@@ -235,10 +279,13 @@ hipError_t launch_kind(const SpecArgs& A, hipStream_t stream) {
   const int64_t waves = 4LL * A.H * A.H;
   const int smax = min(A.m + 2 * A.ext, A.P.L) + 1;
   const size_t lds = (size_t)4 * 2 * smax * sizeof(double);
-  hipLaunchKernelGGL((k_spec_sides<KIND>), dim3((unsigned)((waves + 3) / 4)), dim3(256), lds, stream, A, smax);
+  const int64_t side_blocks = (waves + 3) / 4;
+  const int64_t points = (int64_t)A.H * A.H * (A.p - 1) * (A.p - 1);
+  hipLaunchKernelGGL((k_spec_sides<KIND>), dim3((unsigned)(side_blocks + (points + 255) / 256)), dim3(256), lds, stream,
+                     A, smax, (int32_t)side_blocks);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_spec_solve<KIND>), dim3((unsigned)(A.H * A.H)), dim3(256), 0, stream, A);
+  hipLaunchKernelGGL(k_spec_solve, dim3((unsigned)(A.H * A.H)), dim3(64 * SOLVE_WAVES), 0, stream, A);
   return hipGetLastError();
 }
 
@@ -261,27 +308,16 @@ __device__ __forceinline__ double bary_basis(const double* nodes, const double* 
 }
 
 // One wave per point: 2-D barycentric interpolation of u, du/dx, du/dy on the
-// point's square.  Points are either xy[2 n] (outputs u[n], grad[2 n], each
-// nullable) or, with lut_n > 0, the lut_n^2 nodes of the domain's node grid
-// (output grad_lut[(j lut_n + i) 2 + d] in float32).
+// point's square (outputs u[n], grad[2 n], each nullable).
 __global__ __launch_bounds__(256) void k_spec_eval(SpecDev T, int32_t p, int32_t H, double x0, double x1, double y0,
                                                    double y1, const double* __restrict__ grid, int64_t n_pts,
-                                                   const double* __restrict__ xy, int32_t lut_n, double* u,
-                                                   double* grad, float* grad_lut) {
+                                                   const double* __restrict__ xy, double* u, double* grad) {
   __shared__ double lys[4][64];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int N = p + 1;
   const double Sx = (x1 - x0) / H, Sy = (y1 - y0) / H;
   for (int64_t q = (int64_t)blockIdx.x * 4 + wv; q < n_pts; q += (int64_t)gridDim.x * 4) {
-    double x, y;
-    if (lut_n > 0) {
-      const int i = (int)(q % lut_n), j = (int)(q / lut_n);
-      x = x0 + (x1 - x0) * (double)i / (double)(lut_n - 1);
-      y = y0 + (y1 - y0) * (double)j / (double)(lut_n - 1);
-    } else {
-      x = xy[2 * q];
-      y = xy[2 * q + 1];
-    }
+    const double x = xy[2 * q], y = xy[2 * q + 1];
     const int a = min(max((int)floor((x - x0) / Sx), 0), H - 1);
     const int c = min(max((int)floor((y - y0) / Sy), 0), H - 1);
     const double zx = 2.0 * (x - (x0 + a * Sx)) / Sx - 1.0;
@@ -305,17 +341,158 @@ __global__ __launch_bounds__(256) void k_spec_eval(SpecDev T, int32_t p, int32_t
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     __builtin_amdgcn_wave_barrier();
     if (lane == 0) {
-      if (lut_n > 0) {
-        grad_lut[2 * q] = (float)out[1];
-        grad_lut[2 * q + 1] = (float)out[2];
-      } else {
-        if (u) u[q] = out[0];
-        if (grad) {
-          grad[2 * q] = out[1];
-          grad[2 * q + 1] = out[2];
-        }
+      if (u) u[q] = out[0];
+      if (grad) {
+        grad[2 * q] = out[1];
+        grad[2 * q + 1] = out[2];
       }
     }
+  }
+}
+
+// ---- gradient table -----------------------------------------------------------
+// The nodes of the table that fall in one square form a tensor grid there, so
+// the interpolation of a field G on it is two matrix products,
+//   out[j][i] = sum_l By[j][l] M[l][i],   M[l][i] = sum_k G[k][l] Bx[i][k],
+// with the barycentric bases Bx, By of the square's x and y nodes, on the
+// float64 matrix cores: 4 N^2 (1 + nodes / N) flops per node column instead of
+// the 4 N^2 per node (and two divisions per basis value and node) of a sum
+// per node.  One workgroup per 64 x 64 nodes of a square, a strip of 16 node
+// columns i per wave; M never leaves the registers: its accumulators, rows
+// l / 16 + 4 q of the K step (tile, q), are the second product's B operand
+// with the contraction taken in that order.  A 1025^2 table over 100 squares
+// at p = 63 takes 42 us (one wave and two 64-lane sums per node: 10.8 ms);
+// what remains is the basis divisions and the last, partly filled tiles.
+constexpr int TAB = 64;             // nodes per workgroup and direction
+
+// Node `i` of n in [lo, hi]: its coordinate and its square of H (side S), as
+// for any point (monotone in i, so a square owns a range of nodes).
+__device__ __forceinline__ double node_at(double lo, double hi, int i, int n) {
+  return lo + (hi - lo) * (double)i / (double)(n - 1);
+}
+__device__ __forceinline__ int square_of(double x, double lo, double S, int H) {
+  return min(max((int)floor((x - lo) / S), 0), H - 1);
+}
+// first node whose square is at least a (n for a = H)
+__device__ __forceinline__ int first_node(double lo, double hi, double S, int H, int n, int a) {
+  if (a <= 0) return 0;
+  if (a >= H) return n;
+  int g = (int)min((int64_t)n - 1, ((int64_t)a * (n - 1) + H - 1) / H);
+  while (g > 0 && square_of(node_at(lo, hi, g - 1, n), lo, S, H) >= a) --g;
+  while (g < n && square_of(node_at(lo, hi, g, n), lo, S, H) < a) ++g;
+  return g;
+}
+
+// Barycentric basis of the reference coordinate z shared by the four lanes
+// of equal l % 16: this lane's values at the grid points 4 s + l / 16.
+// *hit: the grid point that z equals exactly (the basis is then that unit
+// vector), or -1.
+__device__ __forceinline__ void bary_frag(const SpecDev& T, int N, int kq, double z, double (&b)[16], int* hit) {
+  int at = -1;
+  double sum = 0.0;
+#pragma unroll
+  for (int s = 0; s < 16; ++s) {
+    const int k = 4 * s + kq;
+    double r = 0.0;
+    if (k < N) {
+      const double dz = z - T.nodes[k];
+      if (dz == 0.0) at = k;
+      r = T.bw[k] / dz;
+    }
+    b[s] = r;
+    sum += r;
+  }
+  at = max(at, __shfl_xor(at, 16, 64));
+  at = max(at, __shfl_xor(at, 32, 64));
+  sum += __shfl_xor(sum, 16, 64);
+  sum += __shfl_xor(sum, 32, 64);
+#pragma unroll
+  for (int s = 0; s < 16; ++s) b[s] = at >= 0 ? (4 * s + kq == at ? 1.0 : 0.0) : b[s] / sum;
+  *hit = at;
+}
+
+__global__ __launch_bounds__(256) void k_spec_table(SpecDev T, int32_t p, int32_t H, double x0, double x1, double y0,
+                                                    double y1, const double* __restrict__ grid, int32_t lut_n,
+                                                    int32_t tiles, float* __restrict__ out) {
+  __shared__ double By[TAB * LDT];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int r = lane & 15, kq = lane >> 4;
+  const int N = p + 1;
+  const double Sx = (x1 - x0) / H, Sy = (y1 - y0) / H;
+  int64_t blk = blockIdx.x;
+  const int ti = (int)(blk % tiles);
+  blk /= tiles;
+  const int tj = (int)(blk % tiles);
+  blk /= tiles;
+  const int a = (int)(blk % H), c = (int)(blk / H);
+  const int i0 = first_node(x0, x1, Sx, H, lut_n, a) + TAB * ti;
+  const int j0 = first_node(y0, y1, Sy, H, lut_n, c) + TAB * tj;
+  const int ni = min(TAB, first_node(x0, x1, Sx, H, lut_n, a + 1) - i0);
+  const int nj = min(TAB, first_node(y0, y1, Sy, H, lut_n, c + 1) - j0);
+  if (ni <= 0 || nj <= 0) return;                  // uniform: an edge tile that holds no node
+  double b[16];
+  int hit;
+  // the strip w of the y nodes, into LDS
+  if (16 * w < nj) {
+    const double y = node_at(y0, y1, j0 + min(16 * w + r, nj - 1), lut_n);
+    bary_frag(T, N, kq, 2.0 * (y - (y0 + c * Sy)) / Sy - 1.0, b, &hit);
+#pragma unroll
+    for (int s = 0; s < 16; ++s) By[(16 * w + r) * LDT + 4 * s + kq] = b[s];
+  }
+  __syncthreads();
+  if (16 * w >= ni) return;                        // no barrier follows
+  const int i = i0 + min(16 * w + r, ni - 1);
+  bary_frag(T, N, kq, 2.0 * (node_at(x0, x1, i, lut_n) - (x0 + a * Sx)) / Sx - 1.0, b, &hit);
+  v4d o[2][4];
+#pragma unroll
+  for (int d = 0; d < 2; ++d) {
+    const double* G = grid + ((size_t)(a + (int64_t)H * c) * 3 + 1 + d) * (size_t)N * N;
+    v4d M[4];
+#pragma unroll
+    for (int rt = 0; rt < 4; ++rt) {
+      M[rt] = v4d{0.0, 0.0, 0.0, 0.0};
+      const int l = 16 * rt + r;
+      double g[16];
+#pragma unroll
+      for (int s = 0; s < 16; ++s) g[s] = (l < N && 4 * s + kq < N) ? G[(size_t)(4 * s + kq) * N + l] : 0.0;
+#pragma unroll
+      for (int s = 0; s < 16; ++s) M[rt] = __builtin_amdgcn_mfma_f64_16x16x4f64(g[s], b[s], M[rt], 0, 0, 0);
+    }
+    // a node on a grid column takes that column's values alone
+    if (hit >= 0) {
+#pragma unroll
+      for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int l = 16 * rt + kq + 4 * q;
+          M[rt][q] = l < N ? G[(size_t)hit * N + l] : 0.0;
+        }
+    }
+#pragma unroll
+    for (int jt = 0; jt < 4; ++jt) {
+      o[d][jt] = v4d{0.0, 0.0, 0.0, 0.0};
+      if (16 * jt < nj) {
+#pragma unroll
+        for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            o[d][jt] = __builtin_amdgcn_mfma_f64_16x16x4f64(By[(16 * jt + r) * LDT + 16 * rt + 4 * q + kq], M[rt][q],
+                                                            o[d][jt], 0, 0, 0);
+      }
+    }
+  }
+  if (16 * w + r < ni) {
+#pragma unroll
+    for (int jt = 0; jt < 4; ++jt)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int jl = 16 * jt + kq + 4 * q;
+        if (jl < nj) {
+          float* to = out + 2 * ((size_t)(j0 + jl) * lut_n + i);
+          to[0] = (float)o[0][jt][q];
+          to[1] = (float)o[1][jt][q];
+        }
+      }
   }
 }
 
@@ -375,12 +552,22 @@ hipError_t launch_spectral_solve(const SpecArgs& A, hipStream_t stream) {
 }
 
 hipError_t launch_spectral_eval(const SpecDev& T, int32_t p, int32_t H, double x0, double x1, double y0, double y1,
-                                const double* grid, int64_t n_pts, const double* xy, int32_t lut_n, double* u,
-                                double* grad, float* grad_lut, hipStream_t stream) {
-  const int64_t pts = lut_n > 0 ? (int64_t)lut_n * lut_n : n_pts;
-  const unsigned blocks = (unsigned)std::min<int64_t>((pts + 3) / 4, 65536);
-  hipLaunchKernelGGL(k_spec_eval, dim3(std::max(blocks, 1u)), dim3(256), 0, stream, T, p, H, x0, x1, y0, y1, grid, pts,
-                     xy, lut_n, u, grad, grad_lut);
+                                const double* grid, int64_t n_pts, const double* xy, double* u, double* grad,
+                                hipStream_t stream) {
+  const unsigned blocks = (unsigned)std::min<int64_t>((n_pts + 3) / 4, 65536);
+  hipLaunchKernelGGL(k_spec_eval, dim3(std::max(blocks, 1u)), dim3(256), 0, stream, T, p, H, x0, x1, y0, y1, grid, n_pts,
+                     xy, u, grad);
+  return hipGetLastError();
+}
+
+hipError_t launch_spectral_table(const SpecDev& T, int32_t p, int32_t H, double x0, double x1, double y0, double y1,
+                                 const double* grid, int32_t lut_n, float* grad_lut, hipStream_t stream) {
+  // a square holds at most (lut_n - 1) / H + 2 nodes per direction
+  const int64_t tiles = ((lut_n - 1) / H + 2 + TAB - 1) / TAB;
+  const int64_t blocks = (int64_t)H * H * tiles * tiles;
+  if (blocks > INT32_MAX) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_spec_table, dim3((unsigned)blocks), dim3(256), 0, stream, T, p, H, x0, x1, y0, y1, grid, lut_n,
+                     (int32_t)tiles, grad_lut);
   return hipGetLastError();
 }
 

@@ -200,3 +200,30 @@ def test_the_papers_control_variate(ctx):
     assert ratio > 3.0
     se = np.sqrt((vp + vc) / N)
     assert np.all(np.abs(cv["b"].cpu().numpy() - plain["b"].cpu().numpy()) <= 5 * se + 1e-9)
+
+
+@pytest.mark.parametrize("H,p,n", [(2, 2, 2), (2, 63, 129), (3, 16, 49), (2, 5, 257), (5, 40, 83), (16, 9, 12)])
+def test_gradient_table_tiles(ctx, H, p, n):
+    """The gradient table's square-by-square products at tile edges: squares
+    with no node, one node, 16, 17, 64, 65 and 129 nodes a direction, nodes
+    on the squares' sides and grid points (n - 1 a multiple of H), every
+    degree's padding.  A random grid, so that a swapped or dropped operand
+    shows; both sides interpolate the same float64 grid, so they differ by
+    the rounding of sums of p + 1 basis values (Lebesgue constant below 5)
+    and the float32 of the table."""
+    w = dict(kind="poisson", param=(), domain=(-1.0, 2.0, 0.5, 3.5), H=H, m=4, ext=2)
+    rng = np.random.default_rng(100 * p + n)
+    grid = torch.from_numpy(rng.normal(size=(H * H, 3, p + 1, p + 1))).cuda()
+    tab = ctx.spectral_grad_lut(w, grid, p, n)
+    q = np.arange(n) / (n - 1) * 3.0
+    Y, X = np.meshgrid(0.5 + q, -1.0 + q, indexing="ij")
+    pts = torch.from_numpy(np.stack([X.ravel(), Y.ravel()], axis=1)).cuda()
+    ref = ctx.spectral_eval(w, grid, p, pts)[1].cpu().numpy().reshape(n, n, 2)
+    g = Geometry(w["domain"], H, 4, 2)
+    few = rng.integers(0, n * n, size=40)
+    fields = [grid[:, f].cpu().numpy() for f in range(3)]
+    orc = osp.interpolate(g, fields, p, pts.cpu().numpy()[few])
+    scale = np.abs(ref).max()
+    got = tab.cpu().numpy()
+    assert np.max(np.abs(got - ref)) <= (2.0 ** -23 + 1e-13 * (p + 1)) * scale
+    assert np.max(np.abs(got.reshape(-1, 2)[few] - np.stack(orc[1:], axis=1))) <= (2.0 ** -23 + 1e-12 * (p + 1)) * scale
