@@ -127,6 +127,9 @@ struct pdd_ctx {
   std::vector<pdd::TuneEntry> tune_cache;
   pdd::DeviceBuffer partial;
   pdd::DeviceBuffer solve_scratch, solve_flag;
+  pdd::DeviceBuffer eval_scratch;    // per-wave sums of the point evaluation,
+  hipEvent_t eval_done = nullptr;    // recorded after its last use
+  hipStream_t eval_stream = nullptr; // on this stream
   pdd::DeviceBuffer collect_scratch, mlp_scratch, calib_scratch, calib_alpha;
   pdd::DeviceBuffer mlp_wide;        // per-workgroup gradients of the multi-workgroup Adam step
   // launch overrides (0 = automatic), set by the tuner
@@ -150,6 +153,7 @@ struct pdd_ctx {
   int ev_used = 0;                   // pairs recorded since pdd_set_timing
   ~pdd_ctx() {
     for (hipEvent_t e : ev_pool) (void)hipEventDestroy(e);
+    if (eval_done) (void)hipEventDestroy(eval_done);
     if (graph_exec) (void)hipGraphExecDestroy(graph_exec);
     if (graph) (void)hipGraphDestroy(graph);
   }

@@ -9,12 +9,20 @@
 // boundary side, else the hat interpolation of the side line's lattice values
 // with the along-side coordinate clamped to the side.
 //
-// One wave per point: lane l integrates paths l, l + 64, ... of the point in
-// turn and keeps float64 sums of the score and its square; a fixed butterfly
-// combines the lanes (deterministic).  Stream: counter (draw, path, point,
-// instance + 2^31).
+// Work split.  A point's paths are cut into `waves_per_pt` contiguous ranges,
+// one wave each (see eval_split), and a lane whose path has exited starts the
+// range's next path at once, as in the assembly: exits are queued in LDS and
+// resolved (side choice, side value) 64 at a time with every lane busy.  The
+// lanes keep float64 sums of the score and its square; a fixed butterfly
+// combines the lanes and, with several waves per point, a second kernel the
+// waves in order (deterministic).  Bound by VALU issue, as the assembly:
+// 20,000 points of 500 paths run at 2.9e11 path-steps/s.  1000 points of 4000
+// VARCOEF paths of about a dozen steps: 0.22 ms (one wave per point, each
+// lane's paths in step with the wave's longest: 1.45 ms).
+// Stream: counter (draw, path, point, instance + 2^31).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
@@ -28,6 +36,10 @@ namespace {
 constexpr int BLK = 256;
 constexpr uint32_t MAX_STEPS = (1u << 24) - 2;
 constexpr uint32_t POINT_STREAM = 1u << 31;
+constexpr int QCAP = 128;        // queued exits per wave (resolved at >= 64)
+// Idle lanes that start new paths (or all of them); measured on paths of 12
+// and 44 steps: 1 within 1 %, 8 1 %, 16 4 % slower.
+constexpr int REFILL = 4;
 
 struct EvalArgs {
   AsmParams P;                 // geometry, coefficients, step and stream parameters
@@ -39,6 +51,8 @@ struct EvalArgs {
   const double* u_knots;
   double* u;
   double* se;
+  int32_t waves_per_pt;
+  double* part;                // waves_per_pt > 1: per wave, sums of s and s^2
 };
 
 __device__ __forceinline__ double wave_sum(double v) {
@@ -85,19 +99,47 @@ __device__ __forceinline__ R line_value(const EvalArgs& A, const KnotDesc& d, in
   return out;
 }
 
+// u and its standard error from the sums over all paths of the point
+__device__ __forceinline__ void write_point(const EvalArgs& A, int64_t pt, double s1, double s2) {
+  const double N = (double)A.n_paths;
+  const double mean = s1 / N;
+  A.u[pt] = mean;
+  if (A.se) A.se[pt] = sqrt(fmax(s2 / N - mean * mean, 0.0) / N);
+}
+
+// A point whose value needs no paths (outside the domain, or on its square's
+// boundary): written as it is, or left for k_eval_sum in the wave's slot, the
+// sum of squares marking it (-1: se = 0, -2: se = NaN).
+__device__ __forceinline__ void no_paths(const EvalArgs& A, int64_t pt, int64_t wave, double v, double se) {
+  if (A.part) {
+    A.part[2 * wave] = v;
+    A.part[2 * wave + 1] = isnan(se) ? -2.0 : -1.0;
+  } else {
+    A.u[pt] = v;
+    if (A.se) A.se[pt] = se;
+  }
+}
+
+template <typename R>
+struct EvalExit {
+  R x, y, Y, Z;
+};
+
 template <int KIND, bool F64>
 __global__ __launch_bounds__(BLK) void k_eval(EvalArgs A) {
   using R = typename std::conditional<F64, double, float>::type;
+  __shared__ EvalExit<R> queue[BLK / 64][QCAP];
+  __shared__ uint32_t queue_fl[BLK / 64][QCAP];
   const AsmParams& P = A.P;
   const int lane = threadIdx.x & 63;
-  const int64_t pt = (int64_t)blockIdx.x * (BLK / 64) + (threadIdx.x >> 6);
+  const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t wave = (int64_t)blockIdx.x * (BLK / 64) + wid;
+  const int64_t pt = wave / A.waves_per_pt;
+  const int64_t part = wave - pt * A.waves_per_pt;
   if (pt >= A.n_pts) return;
   const double px = A.xy[2 * pt], py = A.xy[2 * pt + 1];
   if (!(px >= P.x0 && px <= P.x1 && py >= P.y0 && py <= P.y1)) {
-    if (lane == 0) {
-      A.u[pt] = NAN;
-      if (A.se) A.se[pt] = NAN;
-    }
+    if (lane == 0) no_paths(A, pt, wave, NAN, NAN);
     return;
   }
   // the square holding the point and its description as a "patch"
@@ -124,8 +166,7 @@ __global__ __launch_bounds__(BLK) void k_eval(EvalArgs A) {
   if (on_v || on_h) {
     if (lane == 0) {
       const int o = on_v ? (px == d.line[2] ? 2 : 0) : (py == d.line[3] ? 3 : 1);
-      A.u[pt] = (double)line_value<KIND, R, F64>(A, d, o, on_v ? (R)py : (R)px);
-      if (A.se) A.se[pt] = 0.0;
+      no_paths(A, pt, wave, (double)line_value<KIND, R, F64>(A, d, o, on_v ? (R)py : (R)px), 0.0);
     }
     return;
   }
@@ -135,11 +176,59 @@ __global__ __launch_bounds__(BLK) void k_eval(EvalArgs A) {
   for (int o = 0; o < 4; ++o) e[o] = exit_threshold<KIND, R>(P.coef, P.exit_rule, P.sqrt_h, d, o);
   const R h = (R)P.h, sq = (R)P.sqrt_h;
   double s1 = 0.0, s2 = 0.0;
-  for (int64_t p = lane; p < A.n_paths; p += 64) {
-    R x = (R)px, y = (R)py, Y = (R)1, Z = (R)0;
-    uint32_t j = 0, fl = 0;
-    while (fl == 0) {
-      const U4 r = philox10(j, (uint32_t)p, (uint32_t)pt, A.inst, P.key0, P.key1);
+  EvalExit<R>* Q = queue[wid];
+  uint32_t* Qf = queue_fl[wid];
+  int qn = 0;                            // queued exits
+  // this wave's range of the point's paths
+  uint32_t next = (uint32_t)(A.n_paths * part / A.waves_per_pt);
+  const uint32_t end = (uint32_t)(A.n_paths * (part + 1) / A.waves_per_pt);
+  auto resolve = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    for (int i = lane; i < qn; i += 64) {
+      const EvalExit<R> r = Q[i];
+      const uint32_t fl = Qf[i];
+      const int o = choose_side<R>(r.x, r.y, fl & 1u, (fl >> 1) & 1u, (fl >> 2) & 1u, (fl >> 3) & 1u, d.line);
+      const bool vert = (o == 0 || o == 2);
+      R s;
+      if (isnan(r.x) || isnan(r.y)) {
+        s = (R)NAN;
+      } else {
+        const R val = line_value<KIND, R, F64>(A, d, o, vert ? r.y : r.x);
+        {
+#pragma clang fp contract(off)
+          s = r.Z + r.Y * val;
+        }
+      }
+      s1 += (double)s;
+      s2 += (double)s * (double)s;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    qn = 0;
+  };
+  bool active = false;
+  R x = 0, y = 0, Y = 0, Z = 0;
+  uint32_t p = 0, j = 0;
+  while (true) {
+    const uint64_t idle = __ballot(!active);
+    const int n_idle = __popcll(idle);
+    if (next < end && (n_idle >= REFILL || idle == ~0ull)) {
+      const uint32_t take = min((uint32_t)n_idle, end - next);
+      const uint32_t rank = (uint32_t)__popcll(idle & ((1ull << lane) - 1ull));
+      if (!active && rank < take) {
+        p = next + rank;
+        x = (R)px; y = (R)py; Y = (R)1; Z = (R)0;
+        j = 0;
+        active = true;
+      }
+      next += take;
+    } else if (idle == ~0ull) {
+      break;                             // every path handed out and ended
+    }
+    uint32_t fl = 0;
+    if (active) {
+      const U4 r = philox10(j, p, (uint32_t)pt, A.inst, P.key0, P.key1);
       R z0, z1;
       if constexpr (F64) box_muller(uniform64(r.a), uniform64(r.b), z0, z1);
       else box_muller(uniform32(r.a), uniform32(r.b), z0, z1);
@@ -154,29 +243,58 @@ __global__ __launch_bounds__(BLK) void k_eval(EvalArgs A) {
       ++j;
       if (fl == 0 && 2 * j >= MAX_STEPS) fl = 15u;
     }
-    const int o = choose_side<R>(x, y, fl & 1u, (fl >> 1) & 1u, (fl >> 2) & 1u, (fl >> 3) & 1u, d.line);
-    const bool vert = (o == 0 || o == 2);
-    R s;
-    if (isnan(x) || isnan(y)) {
-      s = (R)NAN;
-    } else {
-      const R val = line_value<KIND, R, F64>(A, d, o, vert ? y : x);
-      {
-#pragma clang fp contract(off)
-        s = Z + Y * val;
+    const uint64_t em = __ballot(fl != 0);
+    if (em != 0) {
+      if (fl != 0) {
+        const int i = qn + __popcll(em & ((1ull << lane) - 1ull));
+        Q[i] = EvalExit<R>{x, y, Y, Z};
+        Qf[i] = fl;
+        active = false;
       }
+      qn += __popcll(em);
+      if (qn >= 64) resolve();
     }
-    s1 += (double)s;
-    s2 += (double)s * (double)s;
   }
+  if (qn > 0) resolve();
   s1 = wave_sum(s1);
   s2 = wave_sum(s2);
   if (lane == 0) {
-    const double N = (double)A.n_paths;
-    const double mean = s1 / N;
-    A.u[pt] = mean;
-    if (A.se) A.se[pt] = sqrt(fmax(s2 / N - mean * mean, 0.0) / N);
+    if (A.part) {
+      A.part[2 * wave] = s1;
+      A.part[2 * wave + 1] = s2;
+    } else {
+      write_point(A, pt, s1, s2);
+    }
   }
+}
+
+// The waves' sums of a point, in wave order (see no_paths for the marks).
+__global__ __launch_bounds__(BLK) void k_eval_sum(EvalArgs A) {
+  const int64_t pt = (int64_t)blockIdx.x * BLK + threadIdx.x;
+  if (pt >= A.n_pts) return;
+  const double* part = A.part + 2 * pt * A.waves_per_pt;
+  if (part[1] < 0.0) {
+    A.u[pt] = part[0];
+    if (A.se) A.se[pt] = part[1] == -1.0 ? 0.0 : NAN;
+    return;
+  }
+  double s1 = 0.0, s2 = 0.0;
+  for (int w = 0; w < A.waves_per_pt; ++w) {
+    s1 += part[2 * w];
+    s2 += part[2 * w + 1];
+  }
+  write_point(A, pt, s1, s2);
+}
+
+// Waves per point: enough waves to fill the device (EVAL_WAVES, six per SIMD),
+// each with at least 64 paths.  More, shorter ranges idle more lanes while a
+// range's last paths end; fewer leave SIMDs without work: 4096, 6144, 8192 and
+// 12288 waves take 0.375, 0.41, 0.42 and 0.51 ms for 50 points of 20,000
+// paths, and 0.241, 0.232, 0.229 and 0.229 ms for 1000 points of 4000.
+constexpr int64_t EVAL_WAVES = 6144;
+int32_t eval_split(int64_t n_pts, int64_t n_paths) {
+  const int64_t fill = (EVAL_WAVES + n_pts - 1) / n_pts, most = (n_paths + 63) / 64;
+  return (int32_t)std::max<int64_t>(1, std::min(fill, most));
 }
 
 template <bool F64>
@@ -216,9 +334,34 @@ pdd_status run_eval_subdomain(pdd_ctx* ctx, const pdd_coeffs& co, const pdd_part
   A.u_knots = u_knots;
   A.u = u;
   A.se = se;
-  const unsigned grid = (unsigned)((n_pts + BLK / 64 - 1) / (BLK / 64));
+  A.waves_per_pt = eval_split(n_pts, run.n_paths);
+  A.part = nullptr;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  // a captured call takes one wave per point, which needs no scratch
+  if (hipStreamIsCapturing(ctx->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusActive) A.waves_per_pt = 1;
+  if (A.waves_per_pt > 1) {
+    const size_t bytes = (size_t)n_pts * A.waves_per_pt * 2 * sizeof(double);
+    if (!ctx->eval_done && (e = hipEventCreateWithFlags(&ctx->eval_done, hipEventDisableTiming)) != hipSuccess)
+      return check_hip(ctx, e, "hipEventCreate(eval)");
+    // the sums of an earlier call on another stream may still be in use
+    if (ctx->eval_stream != ctx->stream && (e = hipStreamWaitEvent(ctx->stream, ctx->eval_done, 0)) != hipSuccess)
+      return check_hip(ctx, e, "hipStreamWaitEvent(eval)");
+    if (bytes > ctx->eval_scratch.bytes) {
+      if ((e = hipStreamSynchronize(ctx->stream)) != hipSuccess) return check_hip(ctx, e, "hipStreamSynchronize");
+      if ((e = ctx->eval_scratch.reserve(bytes)) != hipSuccess) return check_hip(ctx, e, "hipMalloc(eval scratch)");
+    }
+    A.part = ctx->eval_scratch.as<double>();
+  }
+  const int64_t waves = n_pts * A.waves_per_pt;
+  const unsigned grid = (unsigned)((waves + BLK / 64 - 1) / (BLK / 64));
   e = run.precision == PDD_FP64_SAME_STREAM ? launch_kind<true>(A, grid, ctx->stream)
                                             : launch_kind<false>(A, grid, ctx->stream);
+  if (e == hipSuccess && A.part) {
+    hipLaunchKernelGGL(k_eval_sum, dim3((unsigned)((n_pts + BLK - 1) / BLK)), dim3(BLK), 0, ctx->stream, A);
+    e = hipGetLastError();
+    if (e == hipSuccess) e = hipEventRecord(ctx->eval_done, ctx->stream);
+    ctx->eval_stream = ctx->stream;
+  }
   return check_hip(ctx, e, "launch eval_subdomain");
 }
 

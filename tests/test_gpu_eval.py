@@ -105,3 +105,60 @@ def test_pipeline_reproduces_manufactured_solution(ctx):
     se_rms = float(np.sqrt(np.mean(se.cpu().numpy() ** 2)))
     print(f"interface RMSE {rmse_k:.3e}; interior RMSE {rmse:.3e} (rms SE {se_rms:.3e})")
     assert rmse <= 2.0 * rmse_k + 3.0 * se_rms
+
+
+@pytest.mark.parametrize("n_pts,n_paths", [(1, 1), (1, 64), (3, 65), (2, 1000), (130, 129), (8300, 63), (8200, 3)])
+def test_eval_splits_of_the_paths(ctx, n_pts, n_paths):
+    """Points whose paths are cut over several waves (few points, second kernel
+    for the sums) or kept in one (many), with ragged ranges, fewer paths than
+    lanes, points on grid lines and outside the domain: float64 values against
+    the oracle at a sample of the points (1e-12 as above), and every value
+    against the same call made point by point."""
+    w = dict(kind="varcoef", param=(), domain=(0.0, 1.0, 0.0, 1.0), H=4, m=8, ext=4, n_paths=1, h=2e-3, seed=5,
+             precision="fp64", exit_rule="gm", instance=0)
+    g = Geometry(w["domain"], w["H"], w["m"], w["ext"])
+    c = Coefficients("varcoef")
+    rng = np.random.default_rng(n_pts)
+    uk = rng.uniform(-1.0, 1.0, g.n)
+    pts = rng.uniform(0.0, 1.0, size=(n_pts, 2))
+    if n_pts > 2:
+        pts[1] = [0.5, 0.3]
+        pts[2] = [1.5, 0.3]
+    u, se = ctx.eval_subdomain(w, torch.from_numpy(uk).cuda(), torch.from_numpy(pts).cuda(), n_paths)
+    ctx.sync()
+    u, se = u.cpu().numpy(), se.cpu().numpy()
+    if n_pts > 2:
+        assert np.isnan(u[2]) and np.isnan(se[2]) and se[1] == 0.0
+    k = min(n_pts, 12)                   # a leading range keeps the points' stream words
+    keep = [i for i in range(k) if not (n_pts > 2 and i == 2)]
+    inside = pts[:k].copy()
+    if n_pts > 2:
+        inside[2] = [0.4, 0.4]           # its place in the stream is kept, its value not compared
+    ref_u, ref_se, _ = evaluate(g, c, uk, inside, n_paths, w["h"], w["seed"], instance=0, exit_rule="gm")
+    assert np.all(np.abs(u[keep] - ref_u[keep]) <= 1e-12 * (1.0 + np.abs(ref_u[keep])))
+    # the variance of a few paths is a difference of sums: rounding of its square root
+    assert np.allclose(se[keep], ref_se[keep], rtol=1e-9, atol=1e-7)
+
+
+def test_eval_on_two_streams_in_turn(ctx):
+    """Calls that share the context's per-wave sums from two streams, enqueued
+    without a wait between them, give each call's own values."""
+    w = dict(workloads.varcoef(), h=1e-3)
+    g = Geometry(w["domain"], w["H"], w["m"], w["ext"])
+    uk = torch.from_numpy(Coefficients("varcoef").exact(g.x, g.y)).cuda()
+    rng = np.random.default_rng(3)
+    sets = [torch.from_numpy(rng.uniform(0.0, 1.0, size=(n, 2))).cuda() for n in (40, 700)]
+    alone = [ctx.eval_subdomain(w, uk, p, 3000)[0].clone() for p in sets]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    try:
+        for _ in range(5):
+            got = []
+            for st, p in zip(streams, sets):
+                ctx.check(pdd.lib().pdd_set_stream(ctx.h, st.cuda_stream))
+                got.append(ctx.eval_subdomain(w, uk, p, 3000)[0])
+            torch.cuda.synchronize()
+            for a, b in zip(alone, got):
+                assert torch.equal(a, b)
+    finally:
+        ctx.check(pdd.lib().pdd_set_stream(ctx.h, ctx.stream.cuda_stream))
