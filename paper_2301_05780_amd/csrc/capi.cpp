@@ -164,6 +164,10 @@ pdd_status pdd_create(pdd_ctx** out, int32_t device, void* stream) {
   ctx->stream = reinterpret_cast<hipStream_t>(stream);
   ctx->cu_count = prop.multiProcessorCount;
   ctx->arch = prop.gcnArchName;
+  if ((e = hipHostMalloc(&ctx->host_words, 256, hipHostMallocDefault)) != hipSuccess) {
+    delete ctx;
+    return fail(nullptr, PDD_ENOMEM, std::string("hipHostMalloc: ") + hipGetErrorString(e));
+  }
   *out = ctx;
   return PDD_OK;
 }

@@ -126,7 +126,8 @@ struct pdd_ctx {
   bool capturing = false;
   std::vector<pdd::TuneEntry> tune_cache;
   pdd::DeviceBuffer partial;
-  pdd::DeviceBuffer solve_scratch, solve_flag;
+  void* host_words = nullptr;        // pinned, 256 bytes: small results read back
+  pdd::DeviceBuffer solve_scratch;
   pdd::DeviceBuffer eval_scratch;    // per-wave sums of the point evaluation,
   hipEvent_t eval_done = nullptr;    // recorded after its last use
   hipStream_t eval_stream = nullptr; // on this stream
@@ -153,6 +154,7 @@ struct pdd_ctx {
   int ev_used = 0;                   // pairs recorded since pdd_set_timing
   ~pdd_ctx() {
     for (hipEvent_t e : ev_pool) (void)hipEventDestroy(e);
+    if (host_words) (void)hipHostFree(host_words);
     if (eval_done) (void)hipEventDestroy(eval_done);
     if (graph_exec) (void)hipGraphExecDestroy(graph_exec);
     if (graph) (void)hipGraphDestroy(graph);

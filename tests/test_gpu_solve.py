@@ -75,3 +75,68 @@ def test_identity_rows(ctx):
     u, it, rel = ctx.solve(rp, ci, val, b)
     ctx.sync()
     assert rel <= 1e-10 and torch.allclose(u, b, rtol=0, atol=1e-12)
+
+
+def _random_system(n, per_row, seed):
+    """A system like the assembled ones: unit diagonal, rows of negative weights
+    summing to 0.97, plus some rows that are the diagonal alone."""
+    rng = np.random.default_rng(seed)
+    rp, ci, val = [0], [], []
+    for i in range(n):
+        k = 0 if i % 17 == 3 else int(rng.integers(0, 2 * per_row + 1))
+        cols = np.unique(np.append(rng.integers(0, n, size=k), i)).astype(np.int64)
+        wt = rng.uniform(0.1, 1.0, cols.size)
+        off = cols != i
+        s = wt[off].sum()
+        ci.extend(cols.tolist())
+        val.extend(np.where(off, -wt * (0.97 / s if s > 0 else 0.0), 1.0).tolist())
+        rp.append(len(ci))
+    return (np.array(rp, dtype=np.int32), np.array(ci, dtype=np.int32), np.array(val), rng.normal(size=n))
+
+
+@pytest.mark.parametrize("n,per_row", [(1, 1), (2, 1), (63, 5), (1023, 3), (1024, 60), (1025, 9), (2048, 2),
+                                       (2049, 2), (4097, 40), (8193, 30), (16384, 3), (16385, 3)])
+def test_solve_over_sizes(ctx, n, per_row):
+    """The one-launch solve at the edges of its elements per thread (1024 k),
+    with one and with many workgroups, and the kernel-per-operation form just
+    above its largest size: the residual, computed on the host, and up to
+    1025 unknowns the direct solution (the refinement to 1e-12 leaves an error
+    of at most ||G^-1||, below 1 / 0.03 in the max norm, times the residual)."""
+    rp, ci, val, b = _random_system(n, per_row, n)
+    dev = [torch.from_numpy(a).cuda() for a in (rp, ci, val, b)]
+    u, it, rel = ctx.solve(*dev, tol=1e-12)
+    ctx.sync()
+    uh = u.cpu().numpy()
+    assert rel <= 1e-12 and relative_residual(rp, ci, val, b, uh) <= 1.5e-12
+    bound = 1e-12 * np.linalg.norm(b) / 0.03
+    if n <= 1025:
+        assert np.max(np.abs(uh - oracle_solve(rp, ci, val, b))) <= 2.0 * bound
+    # a second solve on the same scratch, from other data
+    u2, _, rel2 = ctx.solve(dev[0], dev[1], dev[2], 2.0 * dev[3], tol=1e-12)
+    assert rel2 <= 1e-12 and np.max(np.abs(u2.cpu().numpy() - 2.0 * uh)) <= 8.0 * bound
+
+
+@pytest.mark.parametrize("n", [40, 1500, 20000])
+def test_malformed_matrices_are_refused(ctx, n):
+    """A column outside [0, n), a decreasing row_ptr and a row_ptr beyond
+    row_ptr[n] give EINVAL and leave u as it was."""
+    rp, ci, val, b = _random_system(n, 2, 1)
+    for change in ("column", "decreasing", "beyond"):
+        r, c = rp.copy(), ci.copy()
+        if change == "column":
+            c[len(c) // 2] = n
+        elif change == "decreasing":
+            r[n // 2] = r[n // 2 - 1] - 1
+        else:
+            r[n - 1] = r[n] + 5
+        u = torch.full((n,), 7.0, dtype=torch.float64, device="cuda")
+        with pytest.raises(pdd.PddError) as e:
+            ctx.solve(*[torch.from_numpy(a).cuda() for a in (r, c, val, b)], u=u)
+        assert e.value.status == pdd.EINVAL
+        ctx.sync()
+        assert bool((u == 7.0).all())
+    bad = b.copy()
+    bad[0] = np.nan
+    with pytest.raises(pdd.PddError) as e:
+        ctx.solve(*[torch.from_numpy(a).cuda() for a in (rp, ci, val, bad)], max_iter=20)
+    assert e.value.status == pdd.ENOTCONV
