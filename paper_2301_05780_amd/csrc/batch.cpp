@@ -99,19 +99,21 @@ pdd_status run_assemble_batch(pdd_ctx* ctx, int32_t n, const pdd_instance* in) {
     }
   }
 
-  // launch shape (slot length known only after the geometry: use the cached one if any)
+  // launch shape
+  bool solo = false;
   int block = ctx->force_block ? ctx->force_block : 256;
   BatchCache* bc = ctx->batch.get();
   const bool capturing = is_capturing(ctx->stream);
 
+  auto rows_for = [&](int blk) { return solo ? blk / 64 : pool_rows_for(ctx, blk); };
   // ticket size from the occupancy of a provisional shape
   auto shape = [&](int slot_len, int& blk, size_t& lds, int64_t& grid) -> pdd_status {
     const int row_len = 4 * slot_len + EX_COUNT;
     blk = block;
-    lds = assemble_lds_bytes(precision, kind, row_len, blk, cv_mode, true, pool_rows_for(ctx, blk));
+    lds = assemble_lds_bytes(precision, kind, row_len, blk, cv_mode, true, rows_for(blk));
     while (lds > 65536 && blk > 64) {
       blk /= 2;
-      lds = assemble_lds_bytes(precision, kind, row_len, blk, cv_mode, true, pool_rows_for(ctx, blk));
+      lds = assemble_lds_bytes(precision, kind, row_len, blk, cv_mode, true, rows_for(blk));
     }
     if (lds > 65536) return bad(ctx, PDD_EUNSUPPORTED, "tally rows exceed the LDS of one workgroup");
     int per_cu = 0;
@@ -121,19 +123,29 @@ pdd_status run_assemble_batch(pdd_ctx* ctx, int32_t n, const pdd_instance* in) {
     return PDD_OK;
   };
 
-  int slot_guess = bc ? bc->slot_len : 0;
-  if (!slot_guess) {
-    for (int32_t i = 0; i < n; ++i)
-      slot_guess = std::max(slot_guess, 2 * in[i].knots.m + 2 * in[i].knots.ext + 1);
-  }
+  int slot_guess = 1;
+  for (int32_t i = 0; i < n; ++i)
+    slot_guess = std::max(slot_guess, (int)slot_length(in[i].part.H, in[i].knots.m, std::max(in[i].knots.ext, 0)));
   int blk;
   size_t lds;
   int64_t grid;
   pdd_status st = shape(slot_guess, blk, lds, grid);
   if (st != PDD_OK) return st;
+  if (cv_mode != PDD_CV_NETWORK && default_shape(ctx)) {
+    const int64_t strided = grid * (blk / 64);
+    solo = true;
+    block = 64;
+    if ((st = shape(slot_guess, blk, lds, grid)) != PDD_OK) return st;
+    if (!solo_pays(total_paths, grid, strided)) {
+      solo = false;
+      block = 256;
+      if ((st = shape(slot_guess, blk, lds, grid)) != PDD_OK) return st;
+    }
+  }
   const int64_t waves = grid * (blk / 64);
   int64_t per_ticket = ctx->force_per_ticket;
-  if (per_ticket <= 0) per_ticket = std::max<int64_t>(256, (total_paths + 7 * waves - 1) / (7 * waves));
+  if (solo) per_ticket = solo_ticket(total_paths, waves);
+  else if (per_ticket <= 0) per_ticket = std::max<int64_t>(256, (total_paths + 7 * waves - 1) / (7 * waves));
 
   if (!bc || !same_inst_tables(*bc, n, in, (int32_t)per_ticket, npk)) {
     if (capturing) return bad(ctx, PDD_EINVAL, "pdd_assemble_batch: tables not cached; run the batch once before capturing");
@@ -243,7 +255,8 @@ pdd_status run_assemble_batch(pdd_ctx* ctx, int32_t n, const pdd_instance* in) {
     if ((e = hipStreamSynchronize(ctx->stream)) != hipSuccess) return check_hip(ctx, e, "hipStreamSynchronize");
     if ((e = ctx->partial.reserve(partial_bytes)) != hipSuccess) return check_hip(ctx, e, "hipMalloc(partial)");
   }
-  if (ctx->schedule == PDD_SCHEDULE_DYNAMIC && !ctx->ticket_counter.ptr) {
+  const bool claims = solo || ctx->schedule == PDD_SCHEDULE_DYNAMIC;
+  if (claims && !ctx->ticket_counter.ptr) {
     if (capturing) return bad(ctx, PDD_EINVAL, "pdd_assemble_batch: counter not allocated; run once before capturing");
     if ((e = ctx->ticket_counter.reserve(8 * sizeof(uint32_t))) != hipSuccess) return check_hip(ctx, e, "hipMalloc(counter)");
     if ((e = hipMemset(ctx->ticket_counter.ptr, 0, 8 * sizeof(uint32_t))) != hipSuccess) return check_hip(ctx, e, "hipMemset(counter)");
@@ -270,9 +283,9 @@ pdd_status run_assemble_batch(pdd_ctx* ctx, int32_t n, const pdd_instance* in) {
   P.partial = ctx->partial.as<double>();
   P.u_ref = nullptr;
   P.lattice = nullptr;
-  P.ticket_counter = ctx->schedule == PDD_SCHEDULE_DYNAMIC ? ctx->ticket_counter.as<uint32_t>() : nullptr;
+  P.ticket_counter = claims ? ctx->ticket_counter.as<uint32_t>() : nullptr;
   P.refill_min = ctx->refill_min;
-  P.pool_rows = pool_rows_for(ctx, blk);
+  P.pool_rows = rows_for(blk);
 
   hipEvent_t t0 = nullptr, t1 = nullptr;
   if (ctx->timing && !capturing && ctx->ev_used < 4096) {

@@ -2,6 +2,7 @@
 #pragma once
 
 #include <algorithm>
+#include <cmath>
 
 #include <hip/hip_runtime.h>
 
@@ -203,6 +204,41 @@ pdd_status run_solve_noalloc(pdd_ctx* ctx, int64_t n, const int32_t* rp, const i
 inline int pool_rows_for(const pdd_ctx* ctx, int block) {
   const int w = block / 64;
   return ctx->spare_rows < 0 ? 2 * w : w + std::min(ctx->spare_rows, w);
+}
+
+
+// Automatic shape of the kernels with a shared row pool (batched launches and
+// the table family) for large runs: workgroups of one wave with one tally row,
+// claiming their tickets from the device counters.  A wave with a single row
+// finishes a ticket before it opens the next one, so a ticket's sums do not
+// depend on which wave runs it or when, and the result is bitwise reproducible
+// although the waves balance themselves.  The fixed stride does not: a SIMD
+// issues its oldest wave first, and the waves end between half and all of the
+// launch.  One row per wave also leaves LDS for more waves.  Measured, 256 threads
+// with two rows per wave and the fixed stride against this: 64-instance batch
+// 157 ms, 75 ms; 4096^2 table with the control variate 43.8 ms, 30.4 ms;
+// 2049^2 table of seven varying fields 12.7 ms, 10.8 ms.
+inline bool default_shape(const pdd_ctx* ctx) {
+  return !ctx->force_block && !ctx->force_grid && !ctx->force_per_ticket && ctx->spare_rows < 0 &&
+         ctx->schedule == PDD_SCHEDULE_STATIC;
+}
+// From how many paths per wave on: a ticket's last paths run with idle lanes,
+// so a small run loses more than the balance gives, unless one row per wave
+// lets many more waves reside than two rows do (`waves` against `strided`).
+// Measured old / new time: equal residency 0.9 at 6750 paths per wave, 1.0 at
+// 8400; 1.25 times the waves 0.97 at 4700; 1.33 times 0.93 at 1480, 1.10 at
+// 5900, 1.35 at 74,000; 2.25 times 1.19 at 2430, 2.7 at 24,000.
+inline bool solo_pays(int64_t paths, int64_t waves, int64_t strided) {
+  const double r = (double)waves / (double)std::max<int64_t>(strided, 1);
+  return (double)paths >= std::max(2048.0, 16384.0 / (r * r * r * r)) * (double)waves;
+}
+// Paths per ticket: fewer cost more drained lanes (about 60 paths' worth per
+// ticket), more a longer wait for the last ticket: 8 sqrt(paths per wave) is
+// 2800 for the 4096^2 table (1250 to 2500: 30.3 ms; 5000: 34), 970 for the
+// 2049^2 table (500: 11.2, 1000: 10.7, 2000: 12.4 ms) and 4650 for the batch
+// (4096: 76.9, 8192: 74.9, whole knots: 78.4 ms).
+inline int64_t solo_ticket(int64_t paths, int64_t waves) {
+  return std::max<int64_t>(64, (int64_t)(8.0 * std::sqrt((double)paths / (double)std::max<int64_t>(waves, 1))));
 }
 
 }  // namespace pdd

@@ -236,10 +236,17 @@ pdd_status run_assemble(pdd_ctx* ctx, const AssembleJob& job) {
   const int slot_len = g.slot_len;
   const int row_len = 4 * slot_len + EX_COUNT;
   const int cv_mode = run.cv ? run.cv->mode : PDD_CV_NONE;
+  // (the RBF sums carry the stencil matrices' conditioning, so their order is
+  // kept; the network's weights would be staged once per wave)
+  const bool may_solo = job.coeffs.kind == PDD_COEF_LUT && !rbf && cv_mode != PDD_CV_NETWORK && default_shape(ctx);
+  bool solo = false;
   int block = ctx->force_block ? ctx->force_block : 256;
   // the tally rows of a workgroup: a shared pool for the table family (spare
   // rows as set on the context), two per wave otherwise
-  auto rows_for = [&](int blk) { return job.coeffs.kind == PDD_COEF_LUT ? pool_rows_for(ctx, blk) : 2 * (blk / 64); };
+  auto rows_for = [&](int blk) {
+    if (solo) return blk / 64;
+    return job.coeffs.kind == PDD_COEF_LUT ? pool_rows_for(ctx, blk) : 2 * (blk / 64);
+  };
   size_t lds = assemble_lds_bytes(run.precision, job.coeffs.kind, row_len, block, cv_mode, false, rows_for(block),
                                   lane_kernel);
   while (lds > 65536 && block > 64) {
@@ -255,6 +262,19 @@ pdd_status run_assemble(pdd_ctx* ctx, const AssembleJob& job) {
   if (e != hipSuccess) return check_hip(ctx, e, "occupancy query");
   per_cu = std::max(per_cu, 1);
   int64_t grid = ctx->force_grid ? ctx->force_grid : (int64_t)ctx->cu_count * per_cu;
+  if (may_solo) {
+    const size_t one = assemble_lds_bytes(run.precision, job.coeffs.kind, row_len, 64, cv_mode, false, 1, lane_kernel);
+    if ((e = assemble_occupancy(run.precision, job.coeffs.kind, cv_mode, false, 64, one, &per_cu, !hk.empty(),
+                                lane_kernel)) != hipSuccess)
+      return check_hip(ctx, e, "occupancy query");
+    const int64_t solo_grid = (int64_t)ctx->cu_count * std::max(per_cu, 1);
+    solo = solo_pays(total, solo_grid, grid * (block / 64));
+    if (solo) {
+      block = 64;
+      lds = one;
+      grid = solo_grid;
+    }
+  }
   const int64_t waves = grid * (block / 64);
 
   // Tabulated coefficients make the path memory-bound on table gathers: order
@@ -265,7 +285,9 @@ pdd_status run_assemble(pdd_ctx* ctx, const AssembleJob& job) {
   // expected first (the static stride stays balanced); at least 256 paths each.
   const bool spatial = job.coeffs.kind == PDD_COEF_LUT;
   int64_t per_ticket = ctx->force_per_ticket;
-  if (per_ticket <= 0) {
+  if (solo) {
+    per_ticket = solo_ticket(total, waves);
+  } else if (per_ticket <= 0) {
     const int64_t per_wave = spatial ? 256 : 7;
     per_ticket = std::max<int64_t>(256, (total + per_wave * waves - 1) / (per_wave * waves));
   }
@@ -367,7 +389,7 @@ pdd_status run_assemble(pdd_ctx* ctx, const AssembleJob& job) {
   }
   P.table_lane = lane_kernel ? 1 : 0;
   if (rbf && (st = prepare_rbf(ctx, g, run, P, capturing)) != PDD_OK) return st;
-  if (ctx->schedule == PDD_SCHEDULE_DYNAMIC) {
+  if (solo || ctx->schedule == PDD_SCHEDULE_DYNAMIC) {
     if (!ctx->ticket_counter.ptr) {
       if (capturing) return bad(ctx, PDD_EINVAL, "pdd_assemble: counter not allocated; run once before capturing");
       if ((e = ctx->ticket_counter.reserve(8 * sizeof(uint32_t))) != hipSuccess) return check_hip(ctx, e, "hipMalloc(counter)");

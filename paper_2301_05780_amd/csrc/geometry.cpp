@@ -18,6 +18,15 @@ int64_t knot_count(int32_t H, int32_t m) {
   return 2 * (h - 1) * (L - 1) - (h - 1) * (h - 1);
 }
 
+int32_t slot_length(int32_t H, int32_t m, int32_t ext) {
+  if (m == 1 && H == 2) return 1;              // the one knot's sides all lie on the boundary
+  const int64_t L = (int64_t)H * m;
+  int64_t longest = 1;                         // sides centred on each grid line
+  for (int64_t c = 1; c < H; ++c)
+    longest = std::max(longest, std::min(L, (c + 1) * m + ext) - std::max<int64_t>(0, (c - 1) * m - ext) + 1);
+  return (int32_t)std::min<int64_t>(longest, INT32_MAX);
+}
+
 SideInfo Geometry::side(int64_t k, int o) const {
   const int32_t xlo = box[4 * k + 0], xhi = box[4 * k + 1];
   const int32_t ylo = box[4 * k + 2], yhi = box[4 * k + 3];

@@ -45,6 +45,8 @@ pdd_status build_geometry(const pdd_partition& part, const pdd_knots& kn, Geomet
                           std::string& err, bool with_pattern = true);
 
 // Number of knots without building anything: 2 (H-1)(H m - 1) - (H-1)^2.
+// Points of the longest interface stencil (Geometry::slot_len, without building it).
+int32_t slot_length(int32_t H, int32_t m, int32_t ext);
 int64_t knot_count(int32_t H, int32_t m);
 
 }  // namespace pdd

@@ -174,3 +174,36 @@ def test_full_batched_workload(ctx):
             assert abs(got["b"][k] - r["b"]) <= 3 * r["se_b"] + 1e-5
     for o in outs:
         assert np.all(np.isfinite(o["b"].cpu().numpy()))
+
+
+@pytest.mark.parametrize("form", ["batch", "table", "all_fields"])
+def test_large_default_launch_is_reproducible_and_equals_the_fixed_stride(ctx, form):
+    """Above the size from which the default launch claims its tickets from
+    the device counters (single-wave workgroups, one tally row each), the sums
+    are still the same bits on every run, and they equal the fixed stride's
+    (the shape that explicit spare rows keep) to float64 summation order."""
+    if form == "batch":
+        ws = [dict(w, n_paths=6000, h=4e-4) for w in workloads.batched()[:12]]
+        arr, outs = ctx.batch_arrays(ws)
+        call = lambda: ctx.assemble_batch(None, arr=arr)     # noqa: E731
+    else:
+        w = dict(workloads.large_lut(), H=8, m=16, ext=8, n_paths=60000, h=1e-3, lut_n=129)
+        tab = workloads.poisson_lut(129) if form == "table" else workloads.varied_lut(129)
+        lut = torch.from_numpy(tab).cuda()
+        out = ctx.assemble(w, lut=lut)
+        outs = [out]
+        call = lambda: ctx.assemble(w, out=out, lut=lut)     # noqa: E731
+    got = []
+    for spare in (-1, -1, -1, 16):                           # 16: two rows per wave, the fixed stride
+        ctx.set_spare_rows(spare)
+        call()
+        ctx.sync()
+        got.append((ctx.last_launch(), [(o["val"].clone(), o["b"].clone(), o["diag"].clone()) for o in outs]))
+    ctx.set_spare_rows(-1)
+    assert got[0][0] == got[1][0] == got[2][0] and got[0][0][1] == 64 and got[3][0][1] > 64
+    for o1, o2, o3, old in zip(*[g[1] for g in got]):
+        for a, b, c, d in zip(o1, o2, o3, old):
+            assert torch.equal(a, b) and torch.equal(a, c)
+            # up to 60,000 float64 additions in another order, all of one sign
+            # or of the magnitude of the largest entry
+            assert float((a - d).abs().max()) <= 1e-12 * float(d.abs().max())
