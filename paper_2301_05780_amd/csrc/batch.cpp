@@ -145,7 +145,7 @@ pdd_status run_assemble_batch(pdd_ctx* ctx, int32_t n, const pdd_instance* in) {
   const int64_t waves = grid * (blk / 64);
   int64_t per_ticket = ctx->force_per_ticket;
   if (solo) per_ticket = solo_ticket(total_paths, waves);
-  else if (per_ticket <= 0) per_ticket = std::max<int64_t>(256, (total_paths + 7 * waves - 1) / (7 * waves));
+  else if (per_ticket <= 0) per_ticket = strided_ticket(total_paths, waves, 0, 0, 7);
 
   if (!bc || !same_inst_tables(*bc, n, in, (int32_t)per_ticket, npk)) {
     if (capturing) return bad(ctx, PDD_EINVAL, "pdd_assemble_batch: tables not cached; run the batch once before capturing");

@@ -281,15 +281,25 @@ pdd_status run_assemble(pdd_ctx* ctx, const AssembleJob& job) {
   // the tickets spatially (subdomains in Morton order) and give each XCD a
   // contiguous share, so the workgroups that share an L2 gather from one
   // neighbourhood; cut knots into more tickets so that the share in flight on
-  // one XCD covers few knots.  Otherwise: about seven tickets per wave, longest
-  // expected first (the static stride stays balanced); at least 256 paths each.
+  // one XCD covers few knots.  Otherwise: about seven tickets per wave (see
+  // strided_ticket), longest expected first.
   const bool spatial = job.coeffs.kind == PDD_COEF_LUT;
   int64_t per_ticket = ctx->force_per_ticket;
   if (solo) {
     per_ticket = solo_ticket(total, waves);
   } else if (per_ticket <= 0) {
     const int64_t per_wave = spatial ? 256 : 7;
-    per_ticket = std::max<int64_t>(256, (total + per_wave * waves - 1) / (per_wave * waves));
+    // (the RBF sums keep their tickets: their order shows through the
+    // conditioning of the stencil matrices)
+    per_ticket = rbf ? std::max<int64_t>(256, (total + per_wave * waves - 1) / (per_wave * waves))
+                     : strided_ticket(total, waves, g.n, run.n_paths_per_knot ? 0 : run.n_paths, per_wave);
+  }
+  // fewer waves than SIMDs: one per workgroup, so that each has a SIMD
+  if (!rbf && cv_mode != PDD_CV_NETWORK && default_shape(ctx) &&
+      total < per_ticket * 4 * (int64_t)ctx->cu_count && block > 64) {
+    block = 64;
+    lds = assemble_lds_bytes(run.precision, job.coeffs.kind, row_len, block, cv_mode, false, rows_for(block), lane_kernel);
+    grid = waves;
   }
 
   // tickets (cached while geometry, path counts, ticket size and order repeat)
