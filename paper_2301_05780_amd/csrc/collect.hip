@@ -1,16 +1,31 @@
 // Training pairs for the control-variate network from the method's own paths.
 //
-// One thread per path (knot k, path p < paths_per_knot), float32, the same
-// random stream and step as the production assembly, so the recorded points
-// lie on the paths that build G and b.  The first `points_per_path` iterates
-// X_n of each path are recorded with Y_n and Z_n; when the path exits at step
-// K the value carried out of the patch is Z_K + Y_K u(exit), with u at the
-// exit interpolated from the solved knot values u0 (hat weights on the exit
-// line) or taken from the boundary datum, and each recorded point gets the
-// tail score (Z_K + Y_K u(exit) - Z_n) / Y_n, whose conditional mean given
-// X_n is u(X_n).  Unused record slots get a NaN target.
+// Path (knot k, p < paths_per_knot), float32, the same random stream and step
+// as the production assembly, so the recorded points lie on the paths that
+// build G and b.  The first `points_per_path` iterates X_n of each path are
+// recorded with Y_n and Z_n; when the path exits at step K the value carried
+// out of the patch is Z_K + Y_K u(exit), with u at the exit interpolated from
+// the solved knot values u0 (hat weights on the exit line) or taken from the
+// boundary datum, and each recorded point gets the tail score
+// (Z_K + Y_K u(exit) - Z_n) / Y_n, whose conditional mean given X_n is u(X_n).
+// Unused record slots get a NaN target.
+//
+// A point's target needs the end of its path, and a path is a few to a few
+// hundred steps of which the first points_per_path are kept.  Holding or
+// writing the points until the exit costs more than stepping them twice:
+//   k_collect_ends    every path to its exit, lanes refilled and exits queued
+//                     as in the assembly; keeps the value and K per path
+//   k_collect_points  one lane per path, its first min(K, points_per_path)
+//                     steps again, the pairs staged in LDS and written out as
+//                     contiguous runs of a path's slots
+// Bound by VALU issue and the 12 B per slot.  1729 knots x 256 paths x 32
+// points (VARCOEF, 15 steps a path, the longest some 300): 165 us for the ends,
+// of which the longest path alone takes about 100, and 49 us for the points (one
+// thread per path, every point's x, y, Y, Z written on its own and Y, Z read
+// back: 387 us).  Computing the next draw beside the steps gained 5 %.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 
 #include "context.h"
@@ -21,6 +36,29 @@ namespace pdd {
 namespace {
 
 constexpr int BLK = 256;
+constexpr int QCAP = 128;            // queued exits per wave (resolved at >= 64)
+constexpr int REFILL = 4;            // idle lanes that start new paths (or all of them)
+// Waves of k_collect_ends: six per SIMD, fewer when a wave would not have a
+// path per lane.  (Small runs end with their longest path, some 300 steps on
+// one lane, so every path starts as early as it can: 442,624 paths take 222 us
+// with 64 paths per wave, 232 with 128, 256 with 192, 271 with 384.)
+constexpr int64_t COLLECT_WAVES = 6144;
+constexpr int64_t COLLECT_RANGE = 64;
+
+// What a path needs of its knot: start, and the strict exit thresholds.
+struct CollectStart {
+  float x, y;
+  float pad0, pad1;
+  float e[4];
+};
+static_assert(sizeof(CollectStart) == COLLECT_START_BYTES, "scratch sizes");
+
+// A path's end: the value carried out of the patch, and K.
+struct CollectEnd {
+  float v;
+  uint32_t K;
+};
+static_assert(sizeof(CollectEnd) == COLLECT_END_BYTES, "scratch sizes");
 
 struct CollectArgs {
   AsmParams P;               // geometry, coefficients, step and stream parameters
@@ -29,50 +67,30 @@ struct CollectArgs {
   int32_t points_per_path;
   const double* u0;          // solved knot values
   uint32_t inst;             // fourth Philox counter word
+  CollectStart* start;       // scratch, per knot
+  CollectEnd* end;           // scratch, per path
   float* xy;                 // 2 per record slot
-  float* yz;                 // scratch: Y_n, Z_n per record slot
   float* target;             // per record slot
 };
 
 template <int KIND>
-__global__ __launch_bounds__(BLK) void k_collect(CollectArgs C) {
+__global__ __launch_bounds__(BLK) void k_collect_start(CollectArgs C) {
+  const int64_t k = (int64_t)blockIdx.x * BLK + threadIdx.x;
+  if (k >= C.n) return;
+  const KnotDesc& d = C.P.desc[k];
+  CollectStart& s = C.start[k];
+  s.x = (float)d.sx;
+  s.y = (float)d.sy;
+#pragma unroll
+  for (int o = 0; o < 4; ++o) s.e[o] = exit_threshold<KIND, float>(C.P.coef, C.P.exit_rule, C.P.sqrt_h, d, o);
+}
+
+// The value carried out of the patch by a path that ended at (x, y) with Y, Z
+// and the sides `fl` flagged.
+template <int KIND>
+__device__ __forceinline__ float exit_score(const CollectArgs& C, const KnotDesc& d, float x, float y, float Y, float Z,
+                                            uint32_t fl) {
   const AsmParams& P = C.P;
-  const int64_t gid = (int64_t)blockIdx.x * BLK + threadIdx.x;
-  if (gid >= C.n * C.paths_per_knot) return;
-  const int64_t k = gid / C.paths_per_knot;
-  const uint32_t p = (uint32_t)(gid % C.paths_per_knot);
-  const KnotDesc& d = P.desc[k];
-  float eb[4];
-  for (int o = 0; o < 4; ++o) eb[o] = exit_threshold<KIND, float>(P.coef, P.exit_rule, P.sqrt_h, d, o);
-  const int S = C.points_per_path;
-  const int64_t slot0 = gid * S;
-  float x = (float)d.sx, y = (float)d.sy, Y = 1.0f, Z = 0.0f;
-  uint32_t j = 0;
-  int recorded = 0;
-  bool ex = false;
-  uint32_t fl = 0;
-  while (!ex) {
-    const U4 r = philox10(j, p, (uint32_t)k, C.inst, P.key0, P.key1);
-    float z0, z1;
-    for (int half = 0; half < 2 && !ex; ++half) {
-      if (half == 0) box_muller(uniform32(r.a), uniform32(r.b), z0, z1);
-      else box_muller(uniform32(r.c), uniform32(r.d), z0, z1);
-      if (recorded < S) {
-        // the network's input: the point in the domain's unit coordinates
-        C.xy[2 * (slot0 + recorded)] = (x - (float)P.x0) * (float)(1.0 / (P.x1 - P.x0));
-        C.xy[2 * (slot0 + recorded) + 1] = (y - (float)P.y0) * (float)(1.0 / (P.y1 - P.y0));
-        C.yz[2 * (slot0 + recorded)] = Y;
-        C.yz[2 * (slot0 + recorded) + 1] = Z;
-        ++recorded;
-      }
-      em_step<KIND, float>(P.coef, (float)P.h, (float)P.sqrt_h, z0, z1, x, y, Y, Z);
-      fl = exit_sides<KIND, float>(P.coef, P.exit_rule, (float)P.sqrt_h, d.line, eb, x, y);
-      ex = fl != 0;
-    }
-    ++j;
-    if (!ex && 2 * j >= (1u << 24) - 2) break;   // safety cap (forced exit below)
-  }
-  if (!ex) fl = 15u;
   const bool fE = fl & 1u, fN = (fl >> 1) & 1u, fW = (fl >> 2) & 1u, fS = (fl >> 3) & 1u;
   const int o = choose_side<float>(x, y, fE, fN, fW, fS, d.line);
   const bool vert = (o == 0 || o == 2);
@@ -103,24 +121,189 @@ __global__ __launch_bounds__(BLK) void k_collect(CollectArgs C) {
       uex += wq * val;
     }
   }
-  const float vout = (isnan(x) || isnan(y)) ? NAN : Z + Y * uex;
-  for (int n = 0; n < S; ++n) {
-    const int64_t sl = slot0 + n;
-    if (n < recorded) {
-      const float Yn = C.yz[2 * sl], Zn = C.yz[2 * sl + 1];
-      C.target[sl] = (vout - Zn) / Yn;
-    } else {
-      C.target[sl] = NAN;
-      C.xy[2 * sl] = 0.0f;
-      C.xy[2 * sl + 1] = 0.0f;
+  return (isnan(x) || isnan(y)) ? NAN : Z + Y * uex;
+}
+
+struct ExitState {
+  float x, y, Y, Z;
+};
+
+// Each wave takes a contiguous range of the path ids (COLLECT_RANGE at most).
+template <int KIND>
+__global__ __launch_bounds__(BLK) void k_collect_ends(CollectArgs C, int64_t waves) {
+  __shared__ ExitState queue[BLK / 64][QCAP];
+  __shared__ uint32_t queue_id[BLK / 64][QCAP], queue_kf[BLK / 64][QCAP];
+  const AsmParams& P = C.P;
+  const int lane = threadIdx.x & 63;
+  const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t wave = (int64_t)blockIdx.x * (BLK / 64) + wid;
+  if (wave >= waves) return;
+  const int64_t total = C.n * C.paths_per_knot;
+  uint32_t next = (uint32_t)(total * wave / waves);
+  const uint32_t stop = (uint32_t)(total * (wave + 1) / waves);
+  ExitState* Q = queue[wid];
+  uint32_t* Qi = queue_id[wid];
+  uint32_t* Qk = queue_kf[wid];
+  int qn = 0;
+  auto resolve = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    for (int i = lane; i < qn; i += 64) {
+      const ExitState r = Q[i];
+      const uint32_t id = Qi[i], kf = Qk[i];
+      const KnotDesc& d = P.desc[id / (uint32_t)C.paths_per_knot];
+      CollectEnd e;
+      e.v = exit_score<KIND>(C, d, r.x, r.y, r.Y, r.Z, kf & 15u);
+      e.K = kf >> 4;
+      C.end[id] = e;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    qn = 0;
+  };
+  bool active = false;
+  uint32_t id = 0, k = 0, p = 0, j = 0;
+  float x = 0, y = 0, Y = 0, Z = 0;
+  float e[4] = {0, 0, 0, 0};
+  while (true) {
+    const uint64_t idle = __ballot(!active);
+    const int n_idle = __popcll(idle);
+    if (next < stop && (n_idle >= REFILL || idle == ~0ull)) {
+      const uint32_t take = min((uint32_t)n_idle, stop - next);
+      const uint32_t rank = (uint32_t)__popcll(idle & ((1ull << lane) - 1ull));
+      if (!active && rank < take) {
+        id = next + rank;
+        k = id / (uint32_t)C.paths_per_knot;
+        p = id - k * (uint32_t)C.paths_per_knot;
+        const CollectStart& s = C.start[k];
+        x = s.x; y = s.y; Y = 1.0f; Z = 0.0f;
+#pragma unroll
+        for (int o = 0; o < 4; ++o) e[o] = s.e[o];
+        j = 0;
+        active = true;
+      }
+      next += take;
+    } else if (idle == ~0ull) {
+      break;
+    }
+    uint32_t fl = 0, K = 0;
+    if (active) {
+      const double* line = P.desc[k].line;
+      const U4 r = philox10(j, p, k, C.inst, P.key0, P.key1);
+      float z0, z1;
+      box_muller(uniform32(r.a), uniform32(r.b), z0, z1);
+      em_step<KIND, float>(P.coef, (float)P.h, (float)P.sqrt_h, z0, z1, x, y, Y, Z);
+      fl = exit_sides<KIND, float>(P.coef, P.exit_rule, (float)P.sqrt_h, line, e, x, y);
+      K = 2 * j + 1;
+      if (fl == 0) {
+        box_muller(uniform32(r.c), uniform32(r.d), z0, z1);
+        em_step<KIND, float>(P.coef, (float)P.h, (float)P.sqrt_h, z0, z1, x, y, Y, Z);
+        fl = exit_sides<KIND, float>(P.coef, P.exit_rule, (float)P.sqrt_h, line, e, x, y);
+        K = 2 * j + 2;
+      }
+      ++j;
+      if (fl == 0 && 2 * j >= (1u << 24) - 2) fl = 15u;   // step cap
+    }
+    const uint64_t em = __ballot(fl != 0);
+    if (em != 0) {
+      if (fl != 0) {
+        const int i = qn + __popcll(em & ((1ull << lane) - 1ull));
+        Q[i] = ExitState{x, y, Y, Z};
+        Qi[i] = id;
+        Qk[i] = (K << 4) | fl;
+        active = false;
+      }
+      qn += __popcll(em);
+      if (qn >= 64) resolve();
     }
   }
+  if (qn > 0) resolve();
+}
+
+// One lane per path: CHUNK points at a time, then the wave writes the chunk's
+// slots, CHUNK consecutive lanes per path.
+constexpr int CHUNK = 8;
+template <int KIND>
+__global__ __launch_bounds__(BLK) void k_collect_points(CollectArgs C) {
+  __shared__ float2 sxy[BLK / 64][64 * (CHUNK + 1)];
+  __shared__ float st[BLK / 64][64 * (CHUNK + 1)];
+  const AsmParams& P = C.P;
+  const int lane = threadIdx.x & 63;
+  const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t total = C.n * C.paths_per_knot;
+  const int64_t first = ((int64_t)blockIdx.x * (BLK / 64) + wid) * 64;
+  if (first >= total) return;
+  const int64_t last = min(first + 64, total);
+  const int S = C.points_per_path;
+  const uint32_t id = (uint32_t)min(first + lane, total - 1);
+  const uint32_t k = id / (uint32_t)C.paths_per_knot, p = id - k * (uint32_t)C.paths_per_knot;
+  const CollectEnd end = C.end[id];
+  const int rec = (int)min(end.K, (uint32_t)S);
+  float x = C.start[k].x, y = C.start[k].y, Y = 1.0f, Z = 0.0f;
+  const float ux = (float)(1.0 / (P.x1 - P.x0)), uy = (float)(1.0 / (P.y1 - P.y0));
+  for (int n0 = 0; n0 < S; n0 += CHUNK) {
+    if (__ballot(n0 < rec) != 0) {
+      U4 r{};
+#pragma unroll
+      for (int c = 0; c < CHUNK; ++c) {
+        const int n = n0 + c;
+        float2 at = make_float2(0.0f, 0.0f);
+        float t = NAN;
+        if (n < rec) {
+          // the network's input: the point in the domain's unit coordinates
+          at.x = (x - (float)P.x0) * ux;
+          at.y = (y - (float)P.y0) * uy;
+          t = (end.v - Z) / Y;
+          if ((c & 1) == 0) r = philox10((uint32_t)n >> 1, p, k, C.inst, P.key0, P.key1);
+          if (n + 1 < rec) {
+            float z0, z1;
+            box_muller(uniform32((c & 1) ? r.c : r.a), uniform32((c & 1) ? r.d : r.b), z0, z1);
+            em_step<KIND, float>(P.coef, (float)P.h, (float)P.sqrt_h, z0, z1, x, y, Y, Z);
+          }
+        }
+        sxy[wid][lane * (CHUNK + 1) + c] = at;
+        st[wid][lane * (CHUNK + 1) + c] = t;
+      }
+    } else {
+#pragma unroll
+      for (int c = 0; c < CHUNK; ++c) {
+        sxy[wid][lane * (CHUNK + 1) + c] = make_float2(0.0f, 0.0f);
+        st[wid][lane * (CHUNK + 1) + c] = NAN;
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int q = 0; q < CHUNK; ++q) {
+      const int path = q * (64 / CHUNK) + lane / CHUNK, c = lane % CHUNK;
+      const int64_t slot = (first + path) * S + n0 + c;
+      if (first + path < last && n0 + c < S) {
+        const float2 at = sxy[wid][path * (CHUNK + 1) + c];
+        C.xy[2 * slot] = at.x;
+        C.xy[2 * slot + 1] = at.y;
+        C.target[slot] = st[wid][path * (CHUNK + 1) + c];
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
+template <int KIND>
+hipError_t launch_kind(const CollectArgs& C, hipStream_t stream) {
+  const int64_t total = C.n * C.paths_per_knot;
+  hipLaunchKernelGGL(k_collect_start<KIND>, dim3((unsigned)((C.n + BLK - 1) / BLK)), dim3(BLK), 0, stream, C);
+  const int64_t waves = std::max<int64_t>(1, std::min<int64_t>(COLLECT_WAVES, (total + COLLECT_RANGE - 1) / COLLECT_RANGE));
+  hipLaunchKernelGGL(k_collect_ends<KIND>, dim3((unsigned)((waves + BLK / 64 - 1) / (BLK / 64))), dim3(BLK), 0, stream, C,
+                     waves);
+  hipLaunchKernelGGL(k_collect_points<KIND>, dim3((unsigned)((total + BLK - 1) / BLK)), dim3(BLK), 0, stream, C);
+  return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_collect(const AsmParams& P, int64_t n, int32_t paths_per_knot, int32_t points_per_path,
-                          uint32_t inst, const double* u0, float* xy, float* yz, float* target, hipStream_t stream) {
+                          uint32_t inst, const double* u0, float* xy, void* scratch, float* target, hipStream_t stream) {
   CollectArgs C;
   C.inst = inst;
   C.P = P;
@@ -128,21 +311,19 @@ hipError_t launch_collect(const AsmParams& P, int64_t n, int32_t paths_per_knot,
   C.paths_per_knot = paths_per_knot;
   C.points_per_path = points_per_path;
   C.u0 = u0;
+  C.start = static_cast<CollectStart*>(scratch);
+  C.end = reinterpret_cast<CollectEnd*>(C.start + n);
   C.xy = xy;
-  C.yz = yz;
   C.target = target;
-  const int64_t threads = n * paths_per_knot;
-  const unsigned grid = (unsigned)((threads + BLK - 1) / BLK);
   switch (P.coef.kind) {
-    case PDD_COEF_POISSON: hipLaunchKernelGGL(k_collect<PDD_COEF_POISSON>, dim3(grid), dim3(BLK), 0, stream, C); break;
-    case PDD_COEF_VARCOEF: hipLaunchKernelGGL(k_collect<PDD_COEF_VARCOEF>, dim3(grid), dim3(BLK), 0, stream, C); break;
-    case PDD_COEF_AMPLITUDE: hipLaunchKernelGGL(k_collect<PDD_COEF_AMPLITUDE>, dim3(grid), dim3(BLK), 0, stream, C); break;
-    case PDD_COEF_LUT: hipLaunchKernelGGL(k_collect<PDD_COEF_LUT>, dim3(grid), dim3(BLK), 0, stream, C); break;
-    case PDD_COEF_CONSTSOL: hipLaunchKernelGGL(k_collect<PDD_COEF_CONSTSOL>, dim3(grid), dim3(BLK), 0, stream, C); break;
-    case PDD_COEF_EQ43: hipLaunchKernelGGL(k_collect<PDD_COEF_EQ43>, dim3(grid), dim3(BLK), 0, stream, C); break;
-    default: hipLaunchKernelGGL(k_collect<PDD_COEF_EXITTIME>, dim3(grid), dim3(BLK), 0, stream, C); break;
+    case PDD_COEF_POISSON: return launch_kind<PDD_COEF_POISSON>(C, stream);
+    case PDD_COEF_VARCOEF: return launch_kind<PDD_COEF_VARCOEF>(C, stream);
+    case PDD_COEF_AMPLITUDE: return launch_kind<PDD_COEF_AMPLITUDE>(C, stream);
+    case PDD_COEF_LUT: return launch_kind<PDD_COEF_LUT>(C, stream);
+    case PDD_COEF_CONSTSOL: return launch_kind<PDD_COEF_CONSTSOL>(C, stream);
+    case PDD_COEF_EQ43: return launch_kind<PDD_COEF_EQ43>(C, stream);
+    default: return launch_kind<PDD_COEF_EXITTIME>(C, stream);
   }
-  return hipGetLastError();
 }
 
 }  // namespace pdd

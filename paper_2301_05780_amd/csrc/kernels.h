@@ -157,8 +157,10 @@ hipError_t assemble_occupancy_rbf(int precision, int kind, int cv_mode, int bloc
                                   int* blocks_per_cu);
 hipError_t launch_finalize(const FinalizeParams& p, hipStream_t stream);
 // Training-pair collection (collect.hip).
+// scratch: COLLECT_START_BYTES per knot and COLLECT_END_BYTES per path
+constexpr size_t COLLECT_START_BYTES = 32, COLLECT_END_BYTES = 8;
 hipError_t launch_collect(const AsmParams& P, int64_t n, int32_t paths_per_knot, int32_t points_per_path,
-                          uint32_t inst, const double* u0, float* xy, float* yz, float* target, hipStream_t stream);
+                          uint32_t inst, const double* u0, float* xy, void* scratch, float* target, hipStream_t stream);
 // Table-wide maxima of |sxx|, |sxy|, |syy| of a LUT (lut.hip): out[0..2]
 // as float bit patterns, out[3] unused.  Two kernels, no memset.
 // Phase II calibration: per-path records (scratch of calibrate_scratch_bytes)

@@ -480,3 +480,36 @@ def test_wide_adam_steps_against_oracle(ctx, batch):
     d_gpu = p.cpu().numpy().astype(np.float64) - th0
     d_ref = th_ref - th0
     assert np.linalg.norm(d_gpu - d_ref) <= 2e-3 * np.linalg.norm(d_ref)
+
+
+@pytest.mark.parametrize("kind,paths,points", [("varcoef", 1, 1), ("varcoef", 3, 7), ("poisson", 65, 9), ("lut", 37, 32),
+                                               ("lut", 2, 300)])
+def test_collected_pairs_ragged_counts(ctx, kind, paths, points):
+    """Training pairs at ragged path and point counts (chunks of eight points,
+    64 paths per wave, more points than steps), closed-form and tabulated
+    coefficients: K, the end and the first points of every path against the
+    paths that the assembly of the same stream dumps (the same float32 step,
+    so the same bits up to the compiler's contraction of the score)."""
+    w = dict(kind=kind, param=(), domain=(0.0, 1.0, 0.0, 1.0), H=3, m=5, ext=2, n_paths=paths, h=2e-3, seed=9,
+             precision="fp32", exit_rule="gm")
+    lut = None
+    if kind == "lut":
+        w["lut_n"] = 33
+        lut = torch.from_numpy(workloads.varied_lut(33)).cuda()
+    n = pdd.pattern(w)[0]
+    zero = torch.zeros(n, dtype=torch.float64, device="cuda")
+    xy, t = ctx.collect(w, zero, paths, points, lut=lut)
+    out = ctx.assemble(dict(w, instance=pdd.COLLECT_STREAM), lut=lut, dump_paths=paths)
+    ctx.sync()
+    d = out["dump"].view(n, paths, pdd.DUMP_WIDTH).cpu().numpy()
+    t = t.cpu().numpy().reshape(n, paths, points)
+    xy = xy.cpu().numpy().reshape(n, paths, points, 2)
+    rec = np.minimum(d[:, :, 0], points).astype(int)
+    used = np.arange(points)[None, None, :] < rec[:, :, None]
+    assert np.array_equal(np.isfinite(t), used)
+    assert np.all(xy[~used] == 0.0)
+    assert np.allclose(xy[:, :, 0], pdd.knot_xy(w)[:, None, :].astype(np.float32), rtol=1e-6)
+    # u0 = 0: the first target is Z_K plus Y_K times the boundary data reached,
+    # which is Z_K itself for exits through interior sides
+    inner = np.abs(t[:, :, 0] - d[:, :, 4]) <= 1e-5 * (1.0 + np.abs(d[:, :, 4]))
+    assert inner.mean() > 0.2
