@@ -57,6 +57,24 @@ pdd_status check_hip(pdd_ctx* ctx, hipError_t e, const char* what) {
   return (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) ? PDD_ENOMEM : PDD_EDEVICE;
 }
 
+pdd_status StreamScratch::acquire(pdd_ctx* ctx, size_t bytes) {
+  hipError_t e;
+  if (!done && (e = hipEventCreateWithFlags(&done, hipEventDisableTiming)) != hipSuccess)
+    return check_hip(ctx, e, "hipEventCreate(scratch)");
+  if (stream != ctx->stream && (e = hipStreamWaitEvent(ctx->stream, done, 0)) != hipSuccess)
+    return check_hip(ctx, e, "hipStreamWaitEvent(scratch)");
+  if (bytes > buf.bytes) {
+    if ((e = hipStreamSynchronize(ctx->stream)) != hipSuccess) return check_hip(ctx, e, "hipStreamSynchronize");
+    if ((e = buf.reserve(bytes)) != hipSuccess) return check_hip(ctx, e, "hipMalloc(scratch)");
+  }
+  return PDD_OK;
+}
+
+pdd_status StreamScratch::release(pdd_ctx* ctx) {
+  stream = ctx->stream;
+  return check_hip(ctx, hipEventRecord(done, ctx->stream), "hipEventRecord(scratch)");
+}
+
 // Geometry of (part, knots), built on the host and uploaded.
 pdd_status build_geo_cache(pdd_ctx* ctx, const pdd_partition& part, const pdd_knots& kn,
                            std::unique_ptr<GeoCache>& out) {

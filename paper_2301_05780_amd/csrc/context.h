@@ -30,6 +30,23 @@ struct DeviceBuffer {
   template <typename T> T* as() const { return static_cast<T*>(ptr); }
 };
 
+// Device scratch of one kind of call, in use by one such call at a time also
+// when the context's stream changes between calls: acquire() makes the stream
+// wait for the last use on another one, release() marks the use just enqueued.
+struct StreamScratch {
+  DeviceBuffer buf;
+  hipEvent_t done = nullptr;
+  hipStream_t stream = nullptr;
+  StreamScratch() = default;
+  StreamScratch(const StreamScratch&) = delete;
+  StreamScratch& operator=(const StreamScratch&) = delete;
+  ~StreamScratch() {
+    if (done) (void)hipEventDestroy(done);
+  }
+  pdd_status acquire(pdd_ctx* ctx, size_t bytes);
+  pdd_status release(pdd_ctx* ctx);
+};
+
 // Host geometry of one (partition, knots) pair and its device copies.
 struct GeoCache {
   pdd_partition part{};
@@ -129,11 +146,9 @@ struct pdd_ctx {
   pdd::DeviceBuffer partial;
   void* host_words = nullptr;        // pinned, 256 bytes: small results read back
   pdd::DeviceBuffer solve_scratch;
-  pdd::DeviceBuffer eval_scratch;    // per-wave sums of the point evaluation,
-  hipEvent_t eval_done = nullptr;    // recorded after its last use
-  hipStream_t eval_stream = nullptr; // on this stream
+  pdd::StreamScratch eval_scratch;   // per-wave sums of the point evaluation
   pdd::DeviceBuffer collect_scratch, mlp_scratch, calib_scratch, calib_alpha;
-  pdd::DeviceBuffer mlp_wide;        // per-workgroup gradients of the multi-workgroup Adam step
+  pdd::StreamScratch mlp_wide;       // the trainer's exchange between workgroups
   // launch overrides (0 = automatic), set by the tuner
   int force_block = 0, force_grid = 0, force_per_ticket = 0;
   int schedule = PDD_SCHEDULE_STATIC;
@@ -156,7 +171,6 @@ struct pdd_ctx {
   ~pdd_ctx() {
     for (hipEvent_t e : ev_pool) (void)hipEventDestroy(e);
     if (host_words) (void)hipHostFree(host_words);
-    if (eval_done) (void)hipEventDestroy(eval_done);
     if (graph_exec) (void)hipGraphExecDestroy(graph_exec);
     if (graph) (void)hipGraphDestroy(graph);
   }

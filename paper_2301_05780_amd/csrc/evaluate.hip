@@ -340,17 +340,8 @@ pdd_status run_eval_subdomain(pdd_ctx* ctx, const pdd_coeffs& co, const pdd_part
   // a captured call takes one wave per point, which needs no scratch
   if (hipStreamIsCapturing(ctx->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusActive) A.waves_per_pt = 1;
   if (A.waves_per_pt > 1) {
-    const size_t bytes = (size_t)n_pts * A.waves_per_pt * 2 * sizeof(double);
-    if (!ctx->eval_done && (e = hipEventCreateWithFlags(&ctx->eval_done, hipEventDisableTiming)) != hipSuccess)
-      return check_hip(ctx, e, "hipEventCreate(eval)");
-    // the sums of an earlier call on another stream may still be in use
-    if (ctx->eval_stream != ctx->stream && (e = hipStreamWaitEvent(ctx->stream, ctx->eval_done, 0)) != hipSuccess)
-      return check_hip(ctx, e, "hipStreamWaitEvent(eval)");
-    if (bytes > ctx->eval_scratch.bytes) {
-      if ((e = hipStreamSynchronize(ctx->stream)) != hipSuccess) return check_hip(ctx, e, "hipStreamSynchronize");
-      if ((e = ctx->eval_scratch.reserve(bytes)) != hipSuccess) return check_hip(ctx, e, "hipMalloc(eval scratch)");
-    }
-    A.part = ctx->eval_scratch.as<double>();
+    if ((st = ctx->eval_scratch.acquire(ctx, (size_t)n_pts * A.waves_per_pt * 2 * sizeof(double))) != PDD_OK) return st;
+    A.part = ctx->eval_scratch.buf.as<double>();
   }
   const int64_t waves = n_pts * A.waves_per_pt;
   const unsigned grid = (unsigned)((waves + BLK / 64 - 1) / (BLK / 64));
@@ -358,9 +349,7 @@ pdd_status run_eval_subdomain(pdd_ctx* ctx, const pdd_coeffs& co, const pdd_part
                                             : launch_kind<false>(A, grid, ctx->stream);
   if (e == hipSuccess && A.part) {
     hipLaunchKernelGGL(k_eval_sum, dim3((unsigned)((n_pts + BLK - 1) / BLK)), dim3(BLK), 0, ctx->stream, A);
-    e = hipGetLastError();
-    if (e == hipSuccess) e = hipEventRecord(ctx->eval_done, ctx->stream);
-    ctx->eval_stream = ctx->stream;
+    if ((e = hipGetLastError()) == hipSuccess) return ctx->eval_scratch.release(ctx);
   }
   return check_hip(ctx, e, "launch eval_subdomain");
 }

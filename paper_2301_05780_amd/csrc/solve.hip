@@ -18,6 +18,7 @@
 #include <mutex>
 
 #include "context.h"
+#include "grid_exchange.h"
 
 namespace pdd {
 
@@ -243,14 +244,11 @@ __global__ void k_zero_words(int32_t* w, int32_t count) {
 // workgroups hold the same bits and take the same branches; only the rows'
 // products are exchanged, twice an iteration (G = 1: never).
 //
-// Exchange: a workgroup stores its rows' products with agent-scope atomic
-// stores (which pass the XCD's own L2), waits for them to complete, and then
-// sets its epoch flag; it reads the others' with agent-scope loads once
-// every flag has reached the epoch.  A buffer is rewritten only two
-// exchanges later, after every workgroup has flagged that it finished
-// reading it.  (Agent fences and plain loads instead: each fence drops the
-// XCD's cached matrix, 2 to 6 times slower.  Words carrying value and exchange
-// number, polled without flags: 2 % slower at 1729 unknowns, 40 % at 15,105.)
+// Exchange (grid_exchange.h): a buffer is rewritten only two exchanges later,
+// after every workgroup has flagged that it finished reading it.  (Agent fences
+// and plain loads instead: each fence drops the XCD's cached matrix, 2 to 6
+// times slower.  Words carrying value and exchange number, polled without flags:
+// 2 % slower at 1729 unknowns, 40 % at 15,105.)
 // The launch is cooperative (the runtime keeps all workgroups resident
 // together) and every wait is bounded: one that runs out ends the kernel and
 // the solve is done by the kernel-per-operation form.
@@ -258,7 +256,6 @@ constexpr int SMALL_T = 1024;
 constexpr int SMALL_N = 16 * SMALL_T;
 constexpr int SMALL_G = 256;               // at most this many workgroups
 constexpr int SMALL_ROWS = 2048;           // rows of one workgroup, at most
-constexpr uint32_t SPIN_LIMIT = 1u << 21;
 constexpr int INNER_MAX = 400;             // BiCGStab iterations of one correction
 constexpr double INNER_TOL = 1e-5;         // and its residual against the correction's right-hand side
 constexpr int OUTER_MAX = 50;
@@ -287,15 +284,6 @@ struct SmallArgs {
   double tol;
   int32_t max_iter;
 };
-
-template <typename T>
-__device__ __forceinline__ void agent_store(T* p, T v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-template <typename T>
-__device__ __forceinline__ T agent_load(const T* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 
 // One DPP step of a sum: each lane adds the value of the lane the control
 // selects (0 outside the row of 16 lanes, or in a row that is masked off).
@@ -372,27 +360,8 @@ __global__ __launch_bounds__(SMALL_T) void k_solve_small(SmallArgs A) {
 
   constexpr int FLY = K <= 2 ? 4 : 8;
   uint32_t epoch = 0;
-  // every workgroup's stores before the call are visible to agent_load after
-  // it; false: a wait ran out (the same for the whole workgroup)
   auto exchange = [&]() __attribute__((always_inline)) -> bool {
-    __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    ++epoch;
-    if (G > 1) {
-      if (tid == 0) agent_store(A.flags + me, epoch);
-      if (w == 0) {
-        uint32_t spins = 0;
-        for (int q = lane; q - lane < G; q += 64) {          // uniform trip count
-          while (__ballot(q < G && agent_load(A.flags + (q < G ? q : 0)) < epoch) != 0) {
-            __builtin_amdgcn_s_sleep(1);
-            if (++spins > SPIN_LIMIT) break;
-          }
-        }
-        if (spins > SPIN_LIMIT && lane == 0) stop = 1;
-      }
-    }
-    __syncthreads();
-    return stop == 0;
+    return grid_exchange(A.flags, G, me, ++epoch, &stop);
   };
   // sums of two values over the workgroup, the same bits in every thread
   int par = 0;

@@ -513,3 +513,61 @@ def test_collected_pairs_ragged_counts(ctx, kind, paths, points):
     # which is Z_K itself for exits through interior sides
     inner = np.abs(t[:, :, 0] - d[:, :, 4]) <= 1e-5 * (1.0 + np.abs(d[:, :, 4]))
     assert inner.mean() > 0.2
+
+
+@pytest.mark.parametrize("batch", [1, 32, 33, 96, 97, 128, 129, 1024, 1025, 1300, 65281])
+def test_adam_steps_over_workgroups(ctx, batch):
+    """The trainer at the edges of its split (points per unit, units per slice,
+    slices, whole slices per workgroup), against the float64 oracle with the
+    bounds of the wide steps above; a captured call, which runs on one
+    workgroup, and calls enqueued from two streams in turn give the same bits
+    as a call of their own: the sums have one order."""
+    steps, lr = 3, 1e-3
+    th0 = _theta(7, noise=0.0)
+    rng = np.random.default_rng(12)
+    n = max(batch, 64)
+    X = rng.uniform(0, 1, size=(n, 2))
+    T = np.cos(2 * X[:, 0]) * X[:, 1] + 0.3 * np.sin(3 * X[:, 1])
+    order = workloads.minibatch_order(n, 3, seed=6)
+    Xf, Tf = X.astype(np.float32).astype(np.float64), T.astype(np.float32).astype(np.float64)
+    th_ref, losses_ref = omlp.train(th0, Xf, Tf, order[:batch * steps], batch, lr)
+    X, T, order = _dev(X, np.float32), _dev(T, np.float32), _dev(order, np.int32)
+
+    def fresh():
+        p = _dev(th0, np.float32)
+        return p, torch.zeros_like(p), torch.zeros_like(p)
+
+    own = fresh()
+    losses = ctx.mlp_train(*own, X, T, order, batch, steps, 0, lr)
+    ctx.sync()
+    assert np.allclose(losses.cpu().numpy(), losses_ref, rtol=1e-3)
+    d_ref = th_ref - th0
+    d_gpu = own[0].cpu().numpy().astype(np.float64) - th0
+    assert np.linalg.norm(d_gpu - d_ref) <= 2e-3 * np.linalg.norm(d_ref)
+
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    sets = [fresh() for _ in range(6)]
+    captured = fresh()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    try:
+        for i, s in enumerate(sets):
+            ctx.check(pdd.lib().pdd_set_stream(ctx.h, streams[i % 2].cuda_stream))
+            ctx.mlp_train(*s, X, T, order, batch, steps, 0, lr)
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=streams[0]):
+            ctx.check(pdd.lib().pdd_set_stream(ctx.h, streams[0].cuda_stream))
+            ctx.mlp_train(*captured, X, T, order, batch, steps, 0, lr)
+        for _ in range(3):
+            for a, b in zip(captured, fresh()):
+                a.copy_(b)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            for a, b in zip(captured, own):
+                assert torch.equal(a, b)
+    finally:
+        ctx.check(pdd.lib().pdd_set_stream(ctx.h, ctx.stream.cuda_stream))
+    for s in sets:
+        for a, b in zip(s, own):
+            assert torch.equal(a, b)
