@@ -148,7 +148,8 @@ struct pdd_ctx {
   pdd::DeviceBuffer solve_scratch;
   pdd::StreamScratch eval_scratch;   // per-wave sums of the point evaluation
   pdd::DeviceBuffer collect_scratch, mlp_scratch, calib_scratch, calib_alpha;
-  pdd::StreamScratch mlp_wide;       // the trainer's exchange between workgroups
+  pdd::StreamScratch mlp_wide;       // the trainer's exchange between workgroups,
+  uint32_t mlp_epoch = 0;            // and no flag in it is above this
   // launch overrides (0 = automatic), set by the tuner
   int force_block = 0, force_grid = 0, force_per_ticket = 0;
   int schedule = PDD_SCHEDULE_STATIC;

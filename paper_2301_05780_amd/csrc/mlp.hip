@@ -187,7 +187,8 @@ struct TrainArgs {
   int32_t units;          // units of the batch (four per slice; of a single slice, those with points)
   float* part;            // several workgroups: the published gradients, GPAD each,
   float* theta;           // the parameters,
-  uint32_t* flags;        // and the epoch flags (zero)
+  uint32_t* flags;        // and the epoch flags, none above
+  uint32_t epoch;         // this
 };
 
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
@@ -278,7 +279,7 @@ __global__ __launch_bounds__(TT) void k_mlp_train(TrainArgs A) {
     }
   }
   const float inv_b = 1.0f / (float)A.batch;
-  uint32_t epoch = 0;
+  uint32_t epoch = A.epoch;
   // this workgroup's units: `u0`, and the one after u
   const int u0 = whole ? 4 * me : me;
   auto after = [&](int u) __attribute__((always_inline)) -> int {
@@ -675,6 +676,8 @@ pdd_status run_mlp_train(pdd_ctx* ctx, float* params, float* m, float* s, int64_
   // a captured call runs on one workgroup: no scratch, no cooperative launch
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(ctx->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusActive) G = 1;
+  // one step of two units: a cooperative launch costs more than the second CU gives (43 us against 39)
+  if (steps == 1 && A.units <= 2) G = 1;
   const void* f = slices == 1 ? reinterpret_cast<const void*>(&k_mlp_train<ONE>)
                   : whole     ? reinterpret_cast<const void*>(&k_mlp_train<WHOLE>)
                               : reinterpret_cast<const void*>(&k_mlp_train<UNITS>);
@@ -687,12 +690,24 @@ pdd_status run_mlp_train(pdd_ctx* ctx, float* params, float* m, float* s, int64_
     return check_hip(ctx, e, "launch mlp_train");
   }
   const size_t part = (size_t)(whole ? slices : slices == 1 ? 8 : A.units) * GPAD;
-  pdd_status st = ctx->mlp_wide.acquire(ctx, (TRAIN_G + PARAM_PAD + part) * sizeof(float));
+  const size_t bytes = (TRAIN_G + PARAM_PAD + part) * sizeof(float);
+  const bool fresh = bytes > ctx->mlp_wide.buf.bytes;
+  pdd_status st = ctx->mlp_wide.acquire(ctx, bytes);
   if (st != PDD_OK) return st;
   A.flags = ctx->mlp_wide.buf.as<uint32_t>();
   A.theta = ctx->mlp_wide.buf.as<float>() + TRAIN_G;
   A.part = A.theta + PARAM_PAD;
-  hipLaunchKernelGGL(k_mlp_zero, dim3(1), dim3(TRAIN_G), 0, ctx->stream, A.flags);
+  // Flags only grow: a call goes on from the epochs of the one before (also of one
+  // that gave up), and they are cleared in a new buffer and before they would wrap.
+  // A clearing kernel before each cooperative launch cost 12 us of a call's 57.
+  const uint32_t epochs = 2u * (uint32_t)steps;
+  if (fresh || ctx->mlp_epoch > UINT32_MAX - epochs) {
+    hipLaunchKernelGGL(k_mlp_zero, dim3(1), dim3(TRAIN_G), 0, ctx->stream, A.flags);
+    if ((e = hipGetLastError()) != hipSuccess) return check_hip(ctx, e, "launch mlp_zero");
+    ctx->mlp_epoch = 0;
+  }
+  A.epoch = ctx->mlp_epoch;
+  ctx->mlp_epoch += epochs;
   e = hipLaunchCooperativeKernel(f, dim3(G), dim3(TT), args, (unsigned)sizeof(TrainLds), ctx->stream);
   if (e != hipSuccess) return check_hip(ctx, e, "launch mlp_train");
   return ctx->mlp_wide.release(ctx);
