@@ -651,16 +651,21 @@ pdd_status pdd_collect_training(pdd_ctx* ctx, const pdd_coeffs* coeffs, const pd
   if ((st = get_lattice(ctx, gc)) != PDD_OK) return st;
   const int64_t slots = gc->g.n * (int64_t)paths_per_knot * points_per_path;
   if (slots > ((int64_t)1 << 31)) return fail(ctx, PDD_EINVAL, "pdd_collect_training: too many record slots");
-  const size_t scratch = (size_t)gc->g.n * COLLECT_START_BYTES + (size_t)gc->g.n * paths_per_knot * COLLECT_END_BYTES;
-  if ((e = ctx->collect_scratch.reserve(scratch)) != hipSuccess)
-    return check_hip(ctx, e, "hipMalloc(collect scratch)");
+  const double cell = std::min(part->x1 - part->x0, part->y1 - part->y0) / part->H;
+  const int64_t paths = gc->g.n * (int64_t)paths_per_knot;
+  void* scratch = nullptr;
+  if (collect_refills(cell * cell / run->h, paths)) {
+    e = ctx->collect_scratch.reserve((size_t)gc->g.n * COLLECT_START_BYTES + (size_t)paths * COLLECT_END_BYTES);
+    if (e != hipSuccess) return check_hip(ctx, e, "hipMalloc(collect scratch)");
+    scratch = ctx->collect_scratch.ptr;
+  }
   AsmParams P;
   fill_asm_params(*gc, *coeffs, *run, P);
   if ((st = prepare_lut_bound(ctx, *coeffs, *run, P, false)) != PDD_OK) return st;
   // the pairs draw from their own stream class (instance word + 2^30), so
   // no assembly with instance < 2^30 reuses the paths the network was fitted on
   e = launch_collect(P, gc->g.n, paths_per_knot, points_per_path, run->instance + PDD_COLLECT_STREAM, u0, xy,
-                     ctx->collect_scratch.ptr, target, ctx->stream);
+                     scratch, target, ctx->stream);
   return check_hip(ctx, e, "launch collect");
 }
 

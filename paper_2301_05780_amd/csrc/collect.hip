@@ -13,16 +13,26 @@
 // A point's target needs the end of its path, and a path is a few to a few
 // hundred steps of which the first points_per_path are kept.  Holding or
 // writing the points until the exit costs more than stepping them twice:
-//   k_collect_ends    every path to its exit, lanes refilled and exits queued
-//                     as in the assembly; keeps the value and K per path
-//   k_collect_points  one lane per path, its first min(K, points_per_path)
-//                     steps again, the pairs staged in LDS and written out as
-//                     contiguous runs of a path's slots
-// Bound by VALU issue and the 12 B per slot.  1729 knots x 256 paths x 32
-// points (VARCOEF, 15 steps a path, the longest some 300): 165 us for the ends,
-// of which the longest path alone takes about 100, and 49 us for the points (one
-// thread per path, every point's x, y, Y, Z written on its own and Y, Z read
-// back: 387 us).  Computing the next draw beside the steps gained 5 %.
+// every path is walked to its exit for its value and K, then its first
+// min(K, points_per_path) steps again, the pairs staged in LDS and written out
+// as contiguous runs of a path's slots.  Two forms with the same bits:
+//   k_collect_whole   one launch, a path per lane from its start to its pairs
+//   k_collect_start, _ends, _points
+//                     the walk to the exit with lanes refilled and exits queued
+//                     as in the assembly, the value and K kept per path; for
+//                     many long paths, where a wave of single paths would wait
+//                     for its longest one (collect_refills)
+// Bound by VALU issue and the 12 B per slot, small calls by their longest path.
+// Times in us (VARCOEF, 16 points; before: one thread per path writing every
+// point's x, y, Y, Z on its own and reading Y, Z back; cell^2 / h steps):
+//   paths, cell^2 / h     before   whole   refilled
+//   2177, 31                23.8    21.5       33.7
+//   299,250, 40              101      51         72
+//   437,280, 20              112      42         70
+//   3,997,875, 90           1764     534        616
+//   299,250, 400             469     388        458
+//   3,997,875, 400          1873    1662       1514
+//   1,999,965, 1500         3090    3074       2469
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -38,12 +48,12 @@ namespace {
 constexpr int BLK = 256;
 constexpr int QCAP = 128;            // queued exits per wave (resolved at >= 64)
 constexpr int REFILL = 4;            // idle lanes that start new paths (or all of them)
-// Waves of k_collect_ends: six per SIMD, fewer when a wave would not have a
-// path per lane.  (Small runs end with their longest path, some 300 steps on
-// one lane, so every path starts as early as it can: 442,624 paths take 222 us
-// with 64 paths per wave, 232 with 128, 256 with 192, 271 with 384.)
-constexpr int64_t COLLECT_WAVES = 6144;
-constexpr int64_t COLLECT_RANGE = 64;
+constexpr int64_t COLLECT_WAVES = 6144;   // of k_collect_ends: six per SIMD
+// The refilled form: from these numbers on (1.0 M paths of 1500: 1949 us against
+// 1815 in one kernel, 2.0 M 2469 against 3074; 4.0 M of 400: 1514 against 1662,
+// of 200: 1004 against 935)
+constexpr double REFILL_STEPS = 300.0;
+constexpr int64_t REFILL_PATHS = 1500000;
 
 // What a path needs of its knot: start, and the strict exit thresholds.
 struct CollectStart {
@@ -67,7 +77,7 @@ struct CollectArgs {
   int32_t points_per_path;
   const double* u0;          // solved knot values
   uint32_t inst;             // fourth Philox counter word
-  CollectStart* start;       // scratch, per knot
+  CollectStart* start;       // scratch, per knot (null: the whole path in one kernel)
   CollectEnd* end;           // scratch, per path
   float* xy;                 // 2 per record slot
   float* target;             // per record slot
@@ -128,7 +138,31 @@ struct ExitState {
   float x, y, Y, Z;
 };
 
-// Each wave takes a contiguous range of the path ids (COLLECT_RANGE at most).
+// Two steps of a path, the second unless the first exits: the flagged sides (0:
+// goes on) and K after them.  Draw j, which is advanced.
+template <int KIND>
+__device__ __forceinline__ uint32_t step_pair(const CollectArgs& C, const double* line, const float (&e)[4], uint32_t k,
+                                              uint32_t p, uint32_t& j, float& x, float& y, float& Y, float& Z,
+                                              uint32_t& K) {
+  const AsmParams& P = C.P;
+  const U4 r = philox10(j, p, k, C.inst, P.key0, P.key1);
+  float z0, z1;
+  box_muller(uniform32(r.a), uniform32(r.b), z0, z1);
+  em_step<KIND, float>(P.coef, (float)P.h, (float)P.sqrt_h, z0, z1, x, y, Y, Z);
+  uint32_t fl = exit_sides<KIND, float>(P.coef, P.exit_rule, (float)P.sqrt_h, line, e, x, y);
+  K = 2 * j + 1;
+  if (fl == 0) {
+    box_muller(uniform32(r.c), uniform32(r.d), z0, z1);
+    em_step<KIND, float>(P.coef, (float)P.h, (float)P.sqrt_h, z0, z1, x, y, Y, Z);
+    fl = exit_sides<KIND, float>(P.coef, P.exit_rule, (float)P.sqrt_h, line, e, x, y);
+    K = 2 * j + 2;
+  }
+  ++j;
+  if (fl == 0 && 2 * j >= (1u << 24) - 2) fl = 15u;   // step cap
+  return fl;
+}
+
+// Each wave takes a contiguous range of the path ids.
 template <int KIND>
 __global__ __launch_bounds__(BLK) void k_collect_ends(CollectArgs C, int64_t waves) {
   __shared__ ExitState queue[BLK / 64][QCAP];
@@ -187,23 +221,7 @@ __global__ __launch_bounds__(BLK) void k_collect_ends(CollectArgs C, int64_t wav
       break;
     }
     uint32_t fl = 0, K = 0;
-    if (active) {
-      const double* line = P.desc[k].line;
-      const U4 r = philox10(j, p, k, C.inst, P.key0, P.key1);
-      float z0, z1;
-      box_muller(uniform32(r.a), uniform32(r.b), z0, z1);
-      em_step<KIND, float>(P.coef, (float)P.h, (float)P.sqrt_h, z0, z1, x, y, Y, Z);
-      fl = exit_sides<KIND, float>(P.coef, P.exit_rule, (float)P.sqrt_h, line, e, x, y);
-      K = 2 * j + 1;
-      if (fl == 0) {
-        box_muller(uniform32(r.c), uniform32(r.d), z0, z1);
-        em_step<KIND, float>(P.coef, (float)P.h, (float)P.sqrt_h, z0, z1, x, y, Y, Z);
-        fl = exit_sides<KIND, float>(P.coef, P.exit_rule, (float)P.sqrt_h, line, e, x, y);
-        K = 2 * j + 2;
-      }
-      ++j;
-      if (fl == 0 && 2 * j >= (1u << 24) - 2) fl = 15u;   // step cap
-    }
+    if (active) fl = step_pair<KIND>(C, P.desc[k].line, e, k, p, j, x, y, Y, Z, K);
     const uint64_t em = __ballot(fl != 0);
     if (em != 0) {
       if (fl != 0) {
@@ -220,26 +238,21 @@ __global__ __launch_bounds__(BLK) void k_collect_ends(CollectArgs C, int64_t wav
   if (qn > 0) resolve();
 }
 
-// One lane per path: CHUNK points at a time, then the wave writes the chunk's
+// The pairs of the paths [first, last), at most 64, one lane per path (id k, p,
+// start x, y, end v, K): CHUNK points at a time, then the wave writes the chunk's
 // slots, CHUNK consecutive lanes per path.
 constexpr int CHUNK = 8;
+struct PairStage {
+  float2 xy[64 * (CHUNK + 1)];
+  float t[64 * (CHUNK + 1)];
+};
 template <int KIND>
-__global__ __launch_bounds__(BLK) void k_collect_points(CollectArgs C) {
-  __shared__ float2 sxy[BLK / 64][64 * (CHUNK + 1)];
-  __shared__ float st[BLK / 64][64 * (CHUNK + 1)];
+__device__ __forceinline__ void write_points(const CollectArgs& C, PairStage& stage, int64_t first, int64_t last, int lane,
+                                             uint32_t k, uint32_t p, float x, float y, const CollectEnd& end) {
   const AsmParams& P = C.P;
-  const int lane = threadIdx.x & 63;
-  const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int64_t total = C.n * C.paths_per_knot;
-  const int64_t first = ((int64_t)blockIdx.x * (BLK / 64) + wid) * 64;
-  if (first >= total) return;
-  const int64_t last = min(first + 64, total);
   const int S = C.points_per_path;
-  const uint32_t id = (uint32_t)min(first + lane, total - 1);
-  const uint32_t k = id / (uint32_t)C.paths_per_knot, p = id - k * (uint32_t)C.paths_per_knot;
-  const CollectEnd end = C.end[id];
   const int rec = (int)min(end.K, (uint32_t)S);
-  float x = C.start[k].x, y = C.start[k].y, Y = 1.0f, Z = 0.0f;
+  float Y = 1.0f, Z = 0.0f;
   const float ux = (float)(1.0 / (P.x1 - P.x0)), uy = (float)(1.0 / (P.y1 - P.y0));
   for (int n0 = 0; n0 < S; n0 += CHUNK) {
     if (__ballot(n0 < rec) != 0) {
@@ -261,14 +274,14 @@ __global__ __launch_bounds__(BLK) void k_collect_points(CollectArgs C) {
             em_step<KIND, float>(P.coef, (float)P.h, (float)P.sqrt_h, z0, z1, x, y, Y, Z);
           }
         }
-        sxy[wid][lane * (CHUNK + 1) + c] = at;
-        st[wid][lane * (CHUNK + 1) + c] = t;
+        stage.xy[lane * (CHUNK + 1) + c] = at;
+        stage.t[lane * (CHUNK + 1) + c] = t;
       }
     } else {
 #pragma unroll
       for (int c = 0; c < CHUNK; ++c) {
-        sxy[wid][lane * (CHUNK + 1) + c] = make_float2(0.0f, 0.0f);
-        st[wid][lane * (CHUNK + 1) + c] = NAN;
+        stage.xy[lane * (CHUNK + 1) + c] = make_float2(0.0f, 0.0f);
+        stage.t[lane * (CHUNK + 1) + c] = NAN;
       }
     }
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -278,10 +291,10 @@ __global__ __launch_bounds__(BLK) void k_collect_points(CollectArgs C) {
       const int path = q * (64 / CHUNK) + lane / CHUNK, c = lane % CHUNK;
       const int64_t slot = (first + path) * S + n0 + c;
       if (first + path < last && n0 + c < S) {
-        const float2 at = sxy[wid][path * (CHUNK + 1) + c];
+        const float2 at = stage.xy[path * (CHUNK + 1) + c];
         C.xy[2 * slot] = at.x;
         C.xy[2 * slot + 1] = at.y;
-        C.target[slot] = st[wid][path * (CHUNK + 1) + c];
+        C.target[slot] = stage.t[path * (CHUNK + 1) + c];
       }
     }
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -290,10 +303,51 @@ __global__ __launch_bounds__(BLK) void k_collect_points(CollectArgs C) {
 }
 
 template <int KIND>
+__global__ __launch_bounds__(BLK) void k_collect_points(CollectArgs C) {
+  __shared__ PairStage stage[BLK / 64];
+  const int lane = threadIdx.x & 63;
+  const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t total = C.n * C.paths_per_knot;
+  const int64_t first = ((int64_t)blockIdx.x * (BLK / 64) + wid) * 64;
+  if (first >= total) return;
+  const uint32_t id = (uint32_t)min(first + lane, total - 1);
+  const uint32_t k = id / (uint32_t)C.paths_per_knot, p = id - k * (uint32_t)C.paths_per_knot;
+  write_points<KIND>(C, stage[wid], first, min(first + 64, total), lane, k, p, C.start[k].x, C.start[k].y, C.end[id]);
+}
+
+// The same in one launch, a path per lane from its start to its pairs.
+template <int KIND>
+__global__ __launch_bounds__(BLK) void k_collect_whole(CollectArgs C) {
+  __shared__ PairStage stage[BLK / 64];
+  const AsmParams& P = C.P;
+  const int lane = threadIdx.x & 63;
+  const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t total = C.n * C.paths_per_knot;
+  const int64_t first = ((int64_t)blockIdx.x * (BLK / 64) + wid) * 64;
+  if (first >= total) return;
+  const uint32_t id = (uint32_t)min(first + lane, total - 1);
+  const uint32_t k = id / (uint32_t)C.paths_per_knot, p = id - k * (uint32_t)C.paths_per_knot;
+  const KnotDesc& d = P.desc[k];
+  float e[4];
+#pragma unroll
+  for (int o = 0; o < 4; ++o) e[o] = exit_threshold<KIND, float>(P.coef, P.exit_rule, P.sqrt_h, d, o);
+  float x = (float)d.sx, y = (float)d.sy, Y = 1.0f, Z = 0.0f;
+  uint32_t j = 0, fl = 0;
+  CollectEnd end{0.0f, 0u};
+  while (fl == 0) fl = step_pair<KIND>(C, d.line, e, k, p, j, x, y, Y, Z, end.K);
+  end.v = exit_score<KIND>(C, d, x, y, Y, Z, fl);
+  write_points<KIND>(C, stage[wid], first, min(first + 64, total), lane, k, p, (float)d.sx, (float)d.sy, end);
+}
+
+template <int KIND>
 hipError_t launch_kind(const CollectArgs& C, hipStream_t stream) {
   const int64_t total = C.n * C.paths_per_knot;
+  if (!C.start) {
+    hipLaunchKernelGGL(k_collect_whole<KIND>, dim3((unsigned)((total + BLK - 1) / BLK)), dim3(BLK), 0, stream, C);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_collect_start<KIND>, dim3((unsigned)((C.n + BLK - 1) / BLK)), dim3(BLK), 0, stream, C);
-  const int64_t waves = std::max<int64_t>(1, std::min<int64_t>(COLLECT_WAVES, (total + COLLECT_RANGE - 1) / COLLECT_RANGE));
+  const int64_t waves = std::min<int64_t>(COLLECT_WAVES, (total + 63) / 64);
   hipLaunchKernelGGL(k_collect_ends<KIND>, dim3((unsigned)((waves + BLK / 64 - 1) / (BLK / 64))), dim3(BLK), 0, stream, C,
                      waves);
   hipLaunchKernelGGL(k_collect_points<KIND>, dim3((unsigned)((total + BLK - 1) / BLK)), dim3(BLK), 0, stream, C);
@@ -301,6 +355,10 @@ hipError_t launch_kind(const CollectArgs& C, hipStream_t stream) {
 }
 
 }  // namespace
+
+bool collect_refills(double cell_steps, int64_t paths) {
+  return cell_steps >= REFILL_STEPS && paths >= REFILL_PATHS;
+}
 
 hipError_t launch_collect(const AsmParams& P, int64_t n, int32_t paths_per_knot, int32_t points_per_path,
                           uint32_t inst, const double* u0, float* xy, void* scratch, float* target, hipStream_t stream) {
@@ -312,7 +370,7 @@ hipError_t launch_collect(const AsmParams& P, int64_t n, int32_t paths_per_knot,
   C.points_per_path = points_per_path;
   C.u0 = u0;
   C.start = static_cast<CollectStart*>(scratch);
-  C.end = reinterpret_cast<CollectEnd*>(C.start + n);
+  C.end = scratch ? reinterpret_cast<CollectEnd*>(C.start + n) : nullptr;
   C.xy = xy;
   C.target = target;
   switch (P.coef.kind) {

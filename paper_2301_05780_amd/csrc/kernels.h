@@ -157,7 +157,10 @@ hipError_t assemble_occupancy_rbf(int precision, int kind, int cv_mode, int bloc
                                   int* blocks_per_cu);
 hipError_t launch_finalize(const FinalizeParams& p, hipStream_t stream);
 // Training-pair collection (collect.hip).
-// scratch: COLLECT_START_BYTES per knot and COLLECT_END_BYTES per path
+// scratch: null, and one kernel walks a path per lane; or COLLECT_START_BYTES per
+// knot and COLLECT_END_BYTES per path where collect_refills() says that refilled
+// lanes pay (cell_steps: squared width of a cell of the partition over h)
+bool collect_refills(double cell_steps, int64_t paths);
 constexpr size_t COLLECT_START_BYTES = 32, COLLECT_END_BYTES = 8;
 hipError_t launch_collect(const AsmParams& P, int64_t n, int32_t paths_per_knot, int32_t points_per_path,
                           uint32_t inst, const double* u0, float* xy, void* scratch, float* target, hipStream_t stream);

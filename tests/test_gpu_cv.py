@@ -571,3 +571,25 @@ def test_adam_steps_over_workgroups(ctx, batch):
     for s in sets:
         for a, b in zip(s, own):
             assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("kind", ["varcoef", "lut"])
+def test_collected_pairs_of_many_long_paths(ctx, kind):
+    """Many long paths take the form with refilled lanes: the pairs of a knot's
+    first paths are those of a call with only these, bit for bit (a path's
+    stream does not depend on how many there are)."""
+    w = dict(kind=kind, param=(), domain=(0.0, 1.0, 0.0, 1.0), H=4, m=8, ext=0, n_paths=64, h=1.0 / 16 / 320, seed=4,
+             precision="fp32", exit_rule="gm")
+    lut = None
+    if kind == "lut":
+        w["lut_n"] = 33
+        lut = torch.from_numpy(workloads.varied_lut(33)).cuda()
+    n = pdd.pattern(w)[0]
+    few, many = 40, 1500000 // n + 1
+    u = torch.linspace(-1.0, 1.0, n, dtype=torch.float64, device="cuda")
+    xy, t = ctx.collect(w, u, many, 3, lut=lut)
+    xy0, t0 = ctx.collect(w, u, few, 3, lut=lut)
+    ctx.sync()
+    assert torch.equal(xy.view(n, many, 3, 2)[:, :few], xy0.view(n, few, 3, 2))
+    assert torch.equal(t.view(n, many, 3)[:, :few].nan_to_num(7.0), t0.view(n, few, 3).nan_to_num(7.0))
+    assert torch.isfinite(t.view(n, many, 3)[:, :, 0]).all()
