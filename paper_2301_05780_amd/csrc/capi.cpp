@@ -522,9 +522,15 @@ pdd_status pdd_calibrate(pdd_ctx* ctx, const pdd_coeffs* coeffs, const pdd_parti
   if ((st = get_lattice(ctx, gc)) != PDD_OK) return st;
   const size_t bytes = calibrate_scratch_bytes(gc->g.n, (int32_t)r.n_paths);
   if (bytes > ((size_t)16 << 30)) return fail(ctx, PDD_EINVAL, "pdd_calibrate: n * n_paths too large (16 GiB scratch)");
-  if ((e = ctx->calib_scratch.reserve(bytes)) != hipSuccess) return check_hip(ctx, e, "hipMalloc(calibration scratch)");
   AsmParams P;
   fill_asm_params(*gc, *coeffs, r, P);
+  const double width = std::min(part->x1 - part->x0, part->y1 - part->y0) / part->H;
+  size_t cells = calibrate_cell_bytes(P, r.precision, gc->g.n * (int64_t)r.n_paths, width * width / r.h, part->H);
+  if (cells && ctx->calib_scratch.reserve(bytes + cells) != hipSuccess) {
+    (void)hipGetLastError();                        // no room: the table as it is
+    cells = 0;
+  }
+  if ((e = ctx->calib_scratch.reserve(bytes)) != hipSuccess) return check_hip(ctx, e, "hipMalloc(calibration scratch)");
   if ((st = prepare_lut_bound(ctx, *coeffs, r, P, false)) != PDD_OK) return st;
   double* alpha = nullptr;
   if (r.interp == PDD_INTERP_RBF_IMQ) {
@@ -535,7 +541,7 @@ pdd_status pdd_calibrate(pdd_ctx* ctx, const pdd_coeffs* coeffs, const pdd_parti
     alpha = ctx->calib_alpha.as<double>();
   }
   e = launch_calibrate(P, r.precision, gc->g.n, (int32_t)r.n_paths, r.instance, u_knots, ctx->calib_scratch.as<double>(),
-                       stats, ctx->stream, alpha, gc->g.slot_len);
+                       stats, ctx->stream, cells != 0, alpha, gc->g.slot_len);
   return check_hip(ctx, e, "launch calibrate");
 }
 

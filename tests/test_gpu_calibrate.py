@@ -151,3 +151,32 @@ def test_rbf_scores_fp64_same_stream(ctx, kappa):
         scale = w["n_paths"] * (1.0 + abs(r[1]) / w["n_paths"]) ** 2
         assert np.all(np.abs(got[k, :3] - r[:3]) <= (1e-11 + S * k_ * 2.0 ** -53) * scale), k
         assert np.array_equal(got[k, 6:], r[6:]), k
+
+
+@pytest.mark.parametrize("kind", ["varcoef", "amplitude"])
+def test_table_by_cells_for_many_long_paths(ctx, kind):
+    """Many long paths read the gradient table cell by cell.  A gradient linear
+    in x and y comes out of a table of any size: 65 nodes (cells) against 2049
+    (too large a patch, the table as it is).  What does not depend on the table
+    is equal; xi differs by the rounding of the nodes and of the weights, below
+    1e-6 per step beside a gradient of size 1, with about 30 steps below 1e-5
+    of its root mean square."""
+    w = dict(kind=kind, param=(0.5,) if kind == "amplitude" else (), domain=(0.0, 1.0, 0.0, 1.0), H=4, m=8, ext=0,
+             n_paths=22700, h=1.0 / 16 / 320, seed=13, precision="fp32", exit_rule="gm")
+    n = pdd.pattern(w)[0]
+    assert n * w["n_paths"] >= 4000000
+    u0 = torch.linspace(-1.0, 1.0, n, dtype=torch.float64, device="cuda")
+    got = []
+    for nodes in (65, 2049):
+        x = torch.linspace(0.0, 1.0, nodes, dtype=torch.float64, device="cuda")
+        Y, X = torch.meshgrid(x, x, indexing="ij")
+        table = torch.stack([1.0 + X - 2.0 * Y, 0.5 - X + 1.5 * Y], dim=-1).float().contiguous()
+        got.append(ctx.calibrate(w, u0, w["n_paths"], cv=pdd.CVSpec("grad_lut", table=table)).cpu().numpy())
+        ctx.sync()
+    cells, rows = got
+    assert np.array_equal(cells[:, [0, 1, 2, 6, 7]], rows[:, [0, 1, 2, 6, 7]])
+    N = w["n_paths"]
+    rms = np.sqrt(rows[:, 4] / N)
+    assert np.all(rms > 0)
+    assert np.all(np.abs(cells[:, 3] - rows[:, 3]) <= 2e-5 * N * rms)
+    assert np.all(np.abs(cells[:, 4] - rows[:, 4]) <= 4e-5 * rows[:, 4])
