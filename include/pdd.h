@@ -450,7 +450,10 @@ pdd_status pdd_spectral_tables(int32_t p, double* decomp_residual, double* inver
  * with key run->seed; run->exit_rule, n_paths_per_knot and dump are not used.
  * stats: device double[n * PDD_CAL_WIDTH], the per-knot sums listed at
  * PDD_CAL_WIDTH, each summed over the knot's paths in a fixed order.  Needs
- * n * n_paths * 40 bytes (plus 512) of scratch, at most 16 GiB. */
+ * n * n_paths * 40 bytes (plus 512) of scratch, at most 16 GiB, and for many
+ * long float32 paths with a gradient table 32 bytes per cell of the table,
+ * without which (no memory, or new to a capture) it reads the table as it is:
+ * the same bits.  */
 pdd_status pdd_calibrate(pdd_ctx* ctx, const pdd_coeffs* coeffs, const pdd_partition* part, const pdd_knots* knots,
                          const pdd_run* run, const double* u_knots, double* stats);
 
@@ -556,10 +559,12 @@ pdd_status pdd_collect_training(pdd_ctx* ctx, const pdd_coeffs* coeffs, const pd
 
 /* ---- launch control and measurement ------------------------------------ */
 
-/* Ticket schedules: STATIC gives wave w the tickets w, w + W, w + 2W, ...
- * (bitwise reproducible sums for a fixed launch shape); DYNAMIC lets waves
- * claim tickets from a device counter (better balance; float64 sums then
- * vary at rounding level between runs). */
+/* Ticket schedules: STATIC gives bitwise reproducible sums for a fixed launch
+ * shape: wave w takes the tickets w, w + W, w + 2W, ..., or, in large table
+ * and batched runs at the default launch settings, single-wave workgroups
+ * with one tally row each claim tickets from device counters, every ticket
+ * summed by itself.  DYNAMIC lets waves of any shape claim tickets (better
+ * balance; float64 sums then vary at rounding level between runs). */
 enum { PDD_SCHEDULE_STATIC = 0, PDD_SCHEDULE_DYNAMIC = 1 };
 
 /* Override the assembly launch shape (0 = automatic): threads per block (a

@@ -526,6 +526,10 @@ pdd_status pdd_calibrate(pdd_ctx* ctx, const pdd_coeffs* coeffs, const pdd_parti
   fill_asm_params(*gc, *coeffs, r, P);
   const double width = std::min(part->x1 - part->x0, part->y1 - part->y0) / part->H;
   size_t cells = calibrate_cell_bytes(P, r.precision, gc->g.n * (int64_t)r.n_paths, width * width / r.h, part->H);
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (cells && bytes + cells > ctx->calib_scratch.bytes && hipStreamIsCapturing(ctx->stream, &cap) == hipSuccess &&
+      cap == hipStreamCaptureStatusActive)
+    cells = 0;                                      // (no allocation in a capture)
   if (cells && ctx->calib_scratch.reserve(bytes + cells) != hipSuccess) {
     (void)hipGetLastError();                        // no room: the table as it is
     cells = 0;
