@@ -709,6 +709,10 @@ pdd_status run_mlp_train(pdd_ctx* ctx, float* params, float* m, float* s, int64_
   A.epoch = ctx->mlp_epoch;
   ctx->mlp_epoch += epochs;
   e = hipLaunchCooperativeKernel(f, dim3(G), dim3(TT), args, (unsigned)sizeof(TrainLds), ctx->stream);
+  if (e == hipErrorCooperativeLaunchTooLarge) {     // a device that does not hold them all: one workgroup, the same bits
+    (void)hipGetLastError();
+    e = hipLaunchKernel(f, dim3(1), dim3(TT), args, sizeof(TrainLds), ctx->stream);
+  }
   if (e != hipSuccess) return check_hip(ctx, e, "launch mlp_train");
   return ctx->mlp_wide.release(ctx);
 }
