@@ -280,6 +280,10 @@ __device__ __forceinline__ void calibrate_body(const CalArgs& C) {
           Q[q] = CalExit<R>{x, y, Y, Z};
           Qi[q] = gid;
           Qk[q] = K << 5 | 16u | fl_em;
+          if (!gm_done) {            // no GM exit at all (a NaN sigma at the side): counted as zeros
+            double* out = C.rec + gid * REC;
+            out[0] = out[2] = out[3] = 0.0;
+          }
           active = false;
         }
         qn += ng + __popcll(me);

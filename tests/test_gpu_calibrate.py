@@ -8,7 +8,7 @@ from paper_2301_05780_amd import pdd, workloads
 from oracle.geometry import Geometry
 from oracle.coeffs import Coefficients
 from oracle import mlp as omlp
-from oracle.calibrate import calibrate as oracle_calibrate, plan
+from oracle.calibrate import calibrate as oracle_calibrate, mixed_paths, plan
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -180,3 +180,42 @@ def test_table_by_cells_for_many_long_paths(ctx, kind):
     assert np.all(rms > 0)
     assert np.all(np.abs(cells[:, 3] - rows[:, 3]) <= 2e-5 * N * rms)
     assert np.all(np.abs(cells[:, 4] - rows[:, 4]) <= 4e-5 * rows[:, 4])
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_path_without_a_gm_exit(ctx, precision):
+    """A NaN sigma at a node just beyond a side (H = 4, 65 nodes: the side's line
+    is node column 16, the NaN in column 17) makes the Gobet-Menozzi test on that
+    side false, so paths leave the patch with no such exit; the patch itself reads
+    no NaN.  Those paths count 0 for phi_GM, xi and K_GM, whatever the calls before
+    left in the context's scratch: float64 against the oracle, float32 by two runs
+    after different calls."""
+    w = dict(kind="lut", param=(), domain=(0.0, 1.0, 0.0, 1.0), H=4, m=4, ext=2, n_paths=96, h=2e-3, seed=11,
+             precision=precision, exit_rule="gm", lut_n=65)
+    tab = workloads.varied_lut(65)
+    tab[:, 17, 0] = np.nan
+    g = Geometry(w["domain"], w["H"], w["m"], w["ext"])
+    left = [k for k in range(g.n) if g.box[k][1] == 0.25]
+    assert left
+    table = _table(4)
+    u0 = _u0(g, Coefficients("poisson"), np.random.default_rng(3))
+    u, lut = torch.from_numpy(u0).cuda(), torch.from_numpy(tab).cuda()
+    clean = torch.from_numpy(workloads.varied_lut(65)).cuda()
+    spec = pdd.CVSpec("grad_lut", table=torch.from_numpy(table).cuda())
+    runs = []
+    for scale in (1e3, -7e5):
+        ctx.calibrate(dict(w, seed=5), scale * torch.ones_like(u), w["n_paths"], cv=spec, lut=clean)
+        runs.append(ctx.calibrate(w, u, w["n_paths"], cv=spec, lut=lut).cpu().numpy())
+    ctx.sync()
+    assert np.array_equal(runs[0], runs[1], equal_nan=True)
+    assert np.isfinite(runs[0][left]).all()
+    if precision == "fp32":
+        return
+    c = Coefficients("lut", (), lut=tab, lut_n=65, domain=w["domain"])
+    gm, _ = mixed_paths(c, g.box[left[0]], (g.x[left[0]], g.y[left[0]]), left[0], 0, w["n_paths"], w["h"], w["seed"])
+    assert (gm["K"] == 0).any() and (gm["K"] > 0).any()
+    ref = oracle_calibrate(g, c, u0, w["n_paths"], w["h"], w["seed"], cv=omlp.GradLutCV(table, w["domain"]), knots=left)
+    for k, r in ref.items():
+        scale = w["n_paths"] * (1.0 + abs(r[1]) / w["n_paths"] + abs(r[3]) / w["n_paths"]) ** 2
+        assert np.all(np.abs(runs[0][k, :6] - r[:6]) <= 1e-11 * scale), k
+        assert np.array_equal(runs[0][k, 6:], r[6:]), k
