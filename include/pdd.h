@@ -525,9 +525,10 @@ pdd_status pdd_mlp_grad(pdd_ctx* ctx, const float* params, int64_t n, const floa
  * workgroup of its own, and the units' gradients are summed in a fixed order
  * (batches up to 1024 as one slice of four units, larger ones as slices of
  * 256 points), so the result does not depend on the workgroups.  Scratch from
- * the context's pool: 141 KB up to a batch of 1024, about 71 KB per 256
- * points from there and 18 KB per 256 points from 65,281 on.  A captured
- * call takes none and runs on one workgroup. */
+ * the context's pool: 143 KB up to a batch of 1024, from there 54 KB and about
+ * 71 KB per 256 points (from 65,281 on 18 KB per 256 points).  A captured call
+ * takes none and runs on one workgroup.  Where a wait between the workgroups runs
+ * out (pdd_set_wait_limit) the first one does the call alone, with the same bits. */
 pdd_status pdd_mlp_train(pdd_ctx* ctx, float* params, float* adam_m, float* adam_s, int64_t n_points,
                          const float* xy, const float* target, const int32_t* order, int64_t n_order, int32_t batch,
                          int32_t steps, int32_t step0, float lr, float* losses);
@@ -612,6 +613,13 @@ pdd_status pdd_set_table_read(pdd_ctx* ctx, int32_t read_all);
 pdd_status pdd_table_fields(pdd_ctx* ctx, uint32_t* varying, int32_t* lane_read);
 /* Shape of the last assembly launch: grid, block and number of tickets. */
 pdd_status pdd_last_launch(const pdd_ctx* ctx, int32_t* grid, int32_t* block, int64_t* tickets);
+/* Waits between the workgroups of one launch (pdd_solve up to 16,384
+ * unknowns, pdd_mlp_train, pdd_mlp_grad) end after `polls` failed polls (-1,
+ * the default: 2^21, some seconds; 0: at once): a long kernel of another
+ * stream can hold the CUs that some of the workgroups need.  The call then goes
+ * on without the others, and more slowly: the trainer on one workgroup, with the
+ * same bits, the solve with a launch per operation. */
+pdd_status pdd_set_wait_limit(pdd_ctx* ctx, int32_t polls);
 /* enable != 0: bracket every assembly kernel launched from now on with a pair
  * of HIP events on the context's stream (up to 4096 launches; the list is
  * cleared by every call of pdd_set_timing).  pdd_kernel_ms waits for the

@@ -679,6 +679,13 @@ pdd_status pdd_collect_training(pdd_ctx* ctx, const pdd_coeffs* coeffs, const pd
   return check_hip(ctx, e, "launch collect");
 }
 
+pdd_status pdd_set_wait_limit(pdd_ctx* ctx, int32_t polls) {
+  if (!ctx) return fail(nullptr, PDD_EINVAL, "pdd_set_wait_limit: null context");
+  if (polls < -1) return fail(ctx, PDD_EINVAL, "pdd_set_wait_limit: polls must be -1 or at least 0");
+  ctx->wait_polls = polls < 0 ? WAIT_POLLS : (uint32_t)polls;
+  return PDD_OK;
+}
+
 pdd_status pdd_set_launch(pdd_ctx* ctx, int32_t block, int32_t grid, int32_t paths_per_ticket,
                           int32_t schedule) {
   if (!ctx) return fail(nullptr, PDD_EINVAL, "pdd_set_launch: null context");

@@ -30,6 +30,9 @@ struct DeviceBuffer {
   template <typename T> T* as() const { return static_cast<T*>(ptr); }
 };
 
+// Polls of a wait between the workgroups of one launch before it is given up (some seconds).
+constexpr uint32_t WAIT_POLLS = 1u << 21;
+
 // Device scratch of one kind of call, in use by one such call at a time also
 // when the context's stream changes between calls: acquire() makes the stream
 // wait for the last use on another one, release() marks the use just enqueued.
@@ -150,6 +153,7 @@ struct pdd_ctx {
   pdd::DeviceBuffer collect_scratch, mlp_scratch, calib_scratch, calib_alpha;
   pdd::StreamScratch mlp_wide;       // the trainer's exchange between workgroups,
   uint32_t mlp_epoch = 0;            // and no flag in it is above this
+  uint32_t wait_polls = pdd::WAIT_POLLS;   // of a wait between the workgroups of one launch
   // launch overrides (0 = automatic), set by the tuner
   int force_block = 0, force_grid = 0, force_per_ticket = 0;
   int schedule = PDD_SCHEDULE_STATIC;

@@ -186,9 +186,10 @@ struct TrainArgs {
   int32_t slice;          // points per slice
   int32_t units;          // units of the batch (four per slice; of a single slice, those with points)
   float* part;            // several workgroups: the published gradients, GPAD each,
-  float* theta;           // the parameters,
+  float* theta;           // several slices: the parameters, and at the end the moments, PARAM_PAD each,
   uint32_t* flags;        // and the epoch flags, none above
   uint32_t epoch;         // this
+  uint32_t polls;         // of a wait between workgroups (grid_exchange.h)
 };
 
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
@@ -246,15 +247,15 @@ __device__ __forceinline__ TrainPoint load_point(const TrainArgs& A, int step, i
 // ONE: a single slice.  UNITS: several.  WHOLE: several, and a workgroup takes the
 // four units of a slice in turn and publishes their sum.
 enum TrainForm { ONE, UNITS, WHOLE };
+// All the steps as workgroup `me` of G.  Only workgroup 0 writes to the caller's
+// arrays: the losses as they come, and the parameters, moments or gradient at the
+// very end.  False: a wait ran out, before that.
 template <TrainForm form>
-__global__ __launch_bounds__(TT) void k_mlp_train(TrainArgs A) {
-  extern __shared__ float tlds[];
-  TrainLds& L = *reinterpret_cast<TrainLds*>(tlds);
+__device__ __forceinline__ bool train_steps(const TrainArgs& A, TrainLds& L, const int G, const int me) {
   float* th = L.th;
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, c = lane & 31;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wt = w >> 1, wb = w & 1;    // waves 0-3: tile (or jb) and half of the units; 4-7: 2 + tile, half
-  const int G = gridDim.x, me = blockIdx.x;
   constexpr bool one = form == ONE, whole = form == WHOLE;
   const int nsl = one ? 1 : (A.batch + A.slice - 1) / A.slice;
   for (int i = tid; i < MLP_PARAMS; i += TT) th[i] = A.params[i];
@@ -511,7 +512,7 @@ __global__ __launch_bounds__(TT) void k_mlp_train(TrainArgs A) {
     const int tstep = A.step0 + step + 1;
     const float c1 = 1.0f - powf(0.9f, (float)tstep);
     const float c2 = 1.0f - powf(0.999f, (float)tstep);
-    if ((late = !grid_exchange(A.flags, G, me, ++epoch, &L.stop))) break;
+    if ((late = !grid_exchange(A.flags, G, me, ++epoch, &L.stop, A.polls))) break;
     // sums of the units and slices in order, then Adam (bias-corrected), beta1 =
     // 0.9, beta2 = 0.999, eps = 1e-8.  The roundings of the step are written out:
     // which product the fused one takes is not left to the compiler.
@@ -548,7 +549,7 @@ __global__ __launch_bounds__(TT) void k_mlp_train(TrainArgs A) {
           th[q] = adam(q, g, mom_m + q, mom_s + q);
         }
       }
-      if (!A.update) return;                          // (the same for every workgroup)
+      if (!A.update) return true;                     // (the same for every workgroup)
       continue;       // the other buffer of gradients is free: all have read it before they published this step's
     }
     for (int i0 = 0; i0 < S * LP; i0 += TT) {           // (uniform)
@@ -572,16 +573,24 @@ __global__ __launch_bounds__(TT) void k_mlp_train(TrainArgs A) {
         }
       }
       if (own && q == MLP_PARAMS) {
-        if (b == 0 && A.losses) A.losses[step] = g;
+        if (b == 0 && G > 1) agent_store(A.theta + q, g);
+        else if (b == 0 && A.losses) A.losses[step] = g;
       } else if (own) {
         const float tq = adam(q, g, resident ? mom_m + item : A.m + q, resident ? mom_s + item : A.s + q);
         if (b == 0) {
-          if (G > 1) agent_store(A.theta + q, tq);
-          else th[q] = tq;
+          if (G > 1) {
+            agent_store(A.theta + q, tq);
+            if (step + 1 == A.steps) {     // the moments for workgroup 0
+              agent_store(A.theta + PARAM_PAD + q, mom_m[item]);
+              agent_store(A.theta + 2 * PARAM_PAD + q, mom_s[item]);
+            }
+          } else {
+            th[q] = tq;
+          }
         }
       }
     }
-    if ((late = !grid_exchange(A.flags, G, me, ++epoch, &L.stop))) break;
+    if ((late = !grid_exchange(A.flags, G, me, ++epoch, &L.stop, A.polls))) break;
     if (G > 1) {
       constexpr int ALL = (MLP_PARAMS + TT - 1) / TT;
       float v[ALL];
@@ -590,21 +599,42 @@ __global__ __launch_bounds__(TT) void k_mlp_train(TrainArgs A) {
 #pragma unroll
       for (int i = 0; i < ALL; ++i)
         if (tid + i * TT < MLP_PARAMS) th[tid + i * TT] = v[i];
+      if (me == 0 && tid == 0 && A.losses) A.losses[step] = agent_load(A.theta + MLP_PARAMS);
     }
   }
-  // a wait that ran out (see grid_exchange.h) leaves no usable parameters
   __syncthreads();
-  if (one && me != 0) return;
-  for (int item = tid; item < S * LP; item += TT) {
-    const int q = q0 + item / LP;
-    if (q < MLP_PARAMS && (item & (LP - 1)) == 0) {
-      if (resident) {
-        A.m[q] = mom_m[item];
-        A.s[q] = mom_s[item];
+  if (late) return false;
+  if constexpr (one) {
+    if (me == 0) {
+      for (int q = tid; q < MLP_PARAMS; q += TT) {
+        A.m[q] = mom_m[q];
+        A.s[q] = mom_s[q];
+        A.params[q] = th[q];
       }
-      A.params[q] = late ? NAN : th[q];
+    }
+    return true;
+  }
+  if (me == 0) {
+    for (int q = tid; q < MLP_PARAMS; q += TT) {
+      if (G > 1) {
+        A.m[q] = agent_load(A.theta + PARAM_PAD + q);
+        A.s[q] = agent_load(A.theta + 2 * PARAM_PAD + q);
+      }
+      A.params[q] = th[q];
     }
   }
+  return true;
+}
+
+// Where a wait ran out (see grid_exchange.h) workgroup 0 does the call by itself,
+// from the start and with the same bits; the others end.
+template <TrainForm form>
+__global__ __launch_bounds__(TT) void k_mlp_train(TrainArgs A) {
+  extern __shared__ float tlds[];
+  TrainLds& L = *reinterpret_cast<TrainLds*>(tlds);
+  if (train_steps<form>(A, L, gridDim.x, blockIdx.x) || blockIdx.x != 0) return;
+  __syncthreads();
+  train_steps<form>(A, L, 1, 0);
 }
 
 __global__ void k_mlp_zero(uint32_t* flags) { flags[threadIdx.x] = 0u; }
@@ -666,6 +696,7 @@ pdd_status run_mlp_train(pdd_ctx* ctx, float* params, float* m, float* s, int64_
   A.update = grad_out ? 0 : 1;
   A.grad_out = grad_out;
   A.losses = losses;
+  A.polls = ctx->wait_polls;
   // the gradient entry keeps one slice at any size
   A.slice = !grad_out && batch > WIDE_BATCH ? WIDE_SLICE : batch;
   const int64_t slices = ((int64_t)batch + A.slice - 1) / A.slice;
@@ -690,13 +721,14 @@ pdd_status run_mlp_train(pdd_ctx* ctx, float* params, float* m, float* s, int64_
     return check_hip(ctx, e, "launch mlp_train");
   }
   const size_t part = (size_t)(whole ? slices : slices == 1 ? 8 : A.units) * GPAD;
-  const size_t bytes = (TRAIN_G + PARAM_PAD + part) * sizeof(float);
+  const size_t theta = slices == 1 ? 0 : 3 * PARAM_PAD;
+  const size_t bytes = (TRAIN_G + theta + part) * sizeof(float);
   const bool fresh = bytes > ctx->mlp_wide.buf.bytes;
   pdd_status st = ctx->mlp_wide.acquire(ctx, bytes);
   if (st != PDD_OK) return st;
   A.flags = ctx->mlp_wide.buf.as<uint32_t>();
   A.theta = ctx->mlp_wide.buf.as<float>() + TRAIN_G;
-  A.part = A.theta + PARAM_PAD;
+  A.part = A.theta + theta;
   // Flags only grow: a call goes on from the epochs of the one before (also of one
   // that gave up), and they are cleared in a new buffer and before they would wrap.
   // A clearing kernel before each cooperative launch cost 12 us of a call's 57.

@@ -283,6 +283,7 @@ struct SmallArgs {
   SmallResult* result;
   double tol;
   int32_t max_iter;
+  uint32_t polls;            // of a wait between workgroups (grid_exchange.h)
 };
 
 // One DPP step of a sum: each lane adds the value of the lane the control
@@ -361,7 +362,7 @@ __global__ __launch_bounds__(SMALL_T) void k_solve_small(SmallArgs A) {
   constexpr int FLY = K <= 2 ? 4 : 8;
   uint32_t epoch = 0;
   auto exchange = [&]() __attribute__((always_inline)) -> bool {
-    return grid_exchange(A.flags, G, me, ++epoch, &stop);
+    return grid_exchange(A.flags, G, me, ++epoch, &stop, A.polls);
   };
   // sums of two values over the workgroup, the same bits in every thread
   int par = 0;
@@ -609,6 +610,7 @@ pdd_status solve_small(pdd_ctx* ctx, int64_t n, int32_t nnz, const int32_t* rp, 
   A.rp = rp; A.ci = ci; A.val = val; A.b = b; A.u = u;
   A.tol = tol;
   A.max_iter = max_iter;
+  A.polls = ctx->wait_polls;
   // result and flags first (cleared together), then the buffers
   int32_t* words = reinterpret_cast<int32_t*>(base);
   A.result = reinterpret_cast<SmallResult*>(base);

@@ -112,6 +112,7 @@ def lib():
             "pdd_set_spare_rows": [vp, i32],
             "pdd_get_spare_rows": [vp, C.POINTER(i32)],
             "pdd_set_table_read": [vp, i32],
+            "pdd_set_wait_limit": [vp, i32],
             "pdd_table_fields": [vp, C.POINTER(C.c_uint32), C.POINTER(i32)],
             "pdd_solve": [vp, i64, vp, vp, vp, vp, vp, f64, i32, C.POINTER(i32), C.POINTER(f64)],
             "pdd_solve_noalloc": [vp, i64, vp, vp, vp, vp, vp, f64, i32, C.POINTER(i32), C.POINTER(f64)],
@@ -313,6 +314,10 @@ class Context:
         """Float32 table assemblies: read only the varying fields when at most
         two vary (default), or always all seven cooperatively."""
         self.check(lib().pdd_set_table_read(self.h, 1 if read_all else 0))
+
+    def set_wait_limit(self, polls=-1):
+        """Polls before a workgroup of a cooperative launch goes on without the others (-1: default, 0: at once)."""
+        self.check(lib().pdd_set_wait_limit(self.h, int(polls)))
 
     def table_fields(self):
         """(bit mask of the fields found varying, lane-per-path read used) of

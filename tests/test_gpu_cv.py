@@ -593,3 +593,52 @@ def test_collected_pairs_of_many_long_paths(ctx, kind):
     assert torch.equal(xy.view(n, many, 3, 2)[:, :few], xy0.view(n, few, 3, 2))
     assert torch.equal(t.view(n, many, 3)[:, :few].nan_to_num(7.0), t0.view(n, few, 3).nan_to_num(7.0))
     assert torch.isfinite(t.view(n, many, 3)[:, :, 0]).all()
+
+
+@pytest.mark.parametrize("polls", [0, 1])
+@pytest.mark.parametrize("batch", [33, 256, 1300, 65281])
+def test_training_goes_on_alone_when_a_wait_runs_out(ctx, batch, polls):
+    """With no polls allowed every wait between the trainer's workgroups is given
+    up, with one most are: parameters, moments and losses have the bits of the
+    undisturbed call, and the call after it too."""
+    steps, lr, n = 3, 1e-3, max(batch, 64)
+    rng = np.random.default_rng(21)
+    X, T = _dev(rng.uniform(0, 1, size=(n, 2)), np.float32), _dev(rng.normal(size=n), np.float32)
+    order = _dev(workloads.minibatch_order(n, 3, seed=6), np.int32)
+
+    def train():
+        p = _dev(_theta(7, noise=0.0), np.float32)
+        m, s = torch.full_like(p, 0.01), torch.full_like(p, 0.02)
+        losses = ctx.mlp_train(p, m, s, X, T, order, batch, steps, 2, lr)
+        ctx.sync()
+        return p, m, s, losses
+
+    own = train()
+    assert all(torch.isfinite(v).all() for v in own)
+    try:
+        ctx.set_wait_limit(polls)
+        alone = [train() for _ in range(3)]
+    finally:
+        ctx.set_wait_limit()
+    for got in alone + [train()]:
+        for a, b in zip(got, own):
+            assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("n", [33, 65, 1000])
+def test_gradient_goes_on_alone_when_a_wait_runs_out(ctx, n):
+    """The gradient entry in the same situation: the same gradient and loss, and
+    the caller's parameters as they were."""
+    rng = np.random.default_rng(22)
+    X, T = _dev(rng.uniform(0, 1, size=(n, 2)), np.float32), _dev(rng.normal(size=n), np.float32)
+    p = _dev(_theta(7), np.float32)
+    before = p.clone()
+    g, loss = ctx.mlp_grad(p, X, T)
+    try:
+        ctx.set_wait_limit(0)
+        g0, loss0 = ctx.mlp_grad(p, X, T)
+    finally:
+        ctx.set_wait_limit()
+    ctx.sync()
+    assert torch.equal(g, g0) and torch.equal(loss, loss0) and torch.equal(p, before)
+    assert torch.isfinite(g).all()

@@ -140,3 +140,21 @@ def test_malformed_matrices_are_refused(ctx, n):
     with pytest.raises(pdd.PddError) as e:
         ctx.solve(*[torch.from_numpy(a).cuda() for a in (rp, ci, val, bad)], max_iter=20)
     assert e.value.status == pdd.ENOTCONV
+
+
+@pytest.mark.parametrize("n,per_row", [(1025, 9), (4097, 40)])
+def test_solve_goes_on_when_a_wait_runs_out(ctx, n, per_row):
+    """With no polls allowed the workgroups of the one-launch solve give up their
+    first wait, and the solve takes the form with a launch per operation: to the
+    same residual, and the solutions within the two residuals' error."""
+    rp, ci, val, b = _random_system(n, per_row, n)
+    dev = [torch.from_numpy(a).cuda() for a in (rp, ci, val, b)]
+    u, _, rel = ctx.solve(*dev, tol=1e-12)
+    try:
+        ctx.set_wait_limit(0)
+        u0, _, rel0 = ctx.solve(*dev, tol=1e-12)
+    finally:
+        ctx.set_wait_limit()
+    assert rel <= 1e-12 and rel0 <= 1e-12
+    assert relative_residual(rp, ci, val, b, u0.cpu().numpy()) <= 1.5e-12
+    assert (u - u0).abs().max().item() <= 4.0 * 1e-12 * np.linalg.norm(b) / 0.03
