@@ -608,8 +608,10 @@ pdd_status pdd_mlp_grad(pdd_ctx* ctx, const float* params, int64_t n, const floa
   if (!ctx) return fail(nullptr, PDD_EINVAL, "pdd_mlp_grad: null context");
   if (!params || !xy || !target || !grad || n < 1 || n > INT32_MAX)
     return fail(ctx, PDD_EINVAL, "pdd_mlp_grad: bad arguments");
+  hipError_t e = hipSetDevice(ctx->device);
+  if (e != hipSuccess) return check_hip(ctx, e, "hipSetDevice");
   // identity order over the n points, one batch of n
-  hipError_t e = ctx->mlp_scratch.reserve((size_t)n * sizeof(int32_t));
+  e = ctx->mlp_scratch.reserve((size_t)n * sizeof(int32_t));
   if (e != hipSuccess) return check_hip(ctx, e, "hipMalloc(mlp scratch)");
   std::vector<int32_t> order(n);
   for (int64_t i = 0; i < n; ++i) order[i] = (int32_t)i;
@@ -627,6 +629,8 @@ pdd_status pdd_mlp_train(pdd_ctx* ctx, float* params, float* adam_m, float* adam
       steps < 0 || step0 < 0 || !(lr > 0.0f))
     return fail(ctx, PDD_EINVAL, "pdd_mlp_train: bad arguments");
   if (steps == 0) return PDD_OK;
+  const hipError_t e = hipSetDevice(ctx->device);
+  if (e != hipSuccess) return check_hip(ctx, e, "hipSetDevice");
   return run_mlp_train(ctx, params, adam_m, adam_s, n_points, xy, target, order, n_order, batch, steps, step0, lr,
                        losses, nullptr);
 }
