@@ -526,9 +526,13 @@ pdd_status pdd_mlp_grad(pdd_ctx* ctx, const float* params, int64_t n, const floa
  * (batches up to 1024 as one slice of four units, larger ones as slices of
  * 256 points), so the result does not depend on the workgroups.  Scratch from
  * the context's pool: 143 KB up to a batch of 1024, from there 54 KB and about
- * 71 KB per 256 points (from 65,281 on 18 KB per 256 points).  A captured call
- * takes none and runs on one workgroup.  Where a wait between the workgroups runs
- * out (pdd_set_wait_limit) the first one does the call alone, with the same bits. */
+ * 71 KB per 256 points (from 65,281 on 18 KB per 256 points).  Where a wait
+ * between the workgroups runs out (pdd_set_wait_limit) the first one does the call
+ * alone, with the same bits.  A captured call runs on one workgroup; a batch
+ * above 1024 as two launches per step, a workgroup per 256 points, with scratch
+ * (18 KB each) that an earlier call of this size or a larger one left, if there
+ * was one (with it such graphs of a context are replayed one after the other).
+ * All forms give the same bits. */
 pdd_status pdd_mlp_train(pdd_ctx* ctx, float* params, float* adam_m, float* adam_s, int64_t n_points,
                          const float* xy, const float* target, const int32_t* order, int64_t n_order, int32_t batch,
                          int32_t steps, int32_t step0, float lr, float* losses);

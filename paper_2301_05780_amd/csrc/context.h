@@ -153,6 +153,7 @@ struct pdd_ctx {
   pdd::DeviceBuffer collect_scratch, mlp_scratch, calib_scratch, calib_alpha;
   pdd::StreamScratch mlp_wide;       // the trainer's exchange between workgroups,
   uint32_t mlp_epoch = 0;            // and no flag in it is above this
+  std::vector<std::unique_ptr<pdd::DeviceBuffer>> mlp_slices;   // gradients of captured training (run_mlp_train)
   uint32_t wait_polls = pdd::WAIT_POLLS;   // of a wait between the workgroups of one launch
   // launch overrides (0 = automatic), set by the tuner
   int force_block = 0, force_grid = 0, force_per_ticket = 0;

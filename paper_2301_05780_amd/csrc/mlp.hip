@@ -14,7 +14,9 @@
 // b2[64], w3[64], b3.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
+#include <memory>
 
 #include "context.h"
 #include "device_common.h"
@@ -637,6 +639,288 @@ __global__ __launch_bounds__(TT) void k_mlp_train(TrainArgs A) {
   train_steps<form>(A, L, 1, 0);
 }
 
+// ---- one workgroup of four waves ----------------------------------------------
+// For calls that a cooperative launch does not suit: a captured one (nothing
+// says that a graph may hold such a launch), and a single step of 33 to 128 points,
+// which is over before the launch of several workgroups has paid.  A wave per unit
+// of the batch, a round of 32 points at a time; the same sums in the same order, the
+// same bits.  us per call or step, the units one after the other on one workgroup
+// of eight waves against this: one step of 96 points 43.6 (three workgroups), 38.2;
+// the gradient of 100 points 58.3, 47.7; captured steps of 64 points 20.2, 18.6; 128 37.0,
+// 18.7; 256 42.2, 31.5; 1024 143, 108.  Up to 32 points (one unit) the eight waves are
+// faster: 11.9, 18.6.
+// A captured batch above WIDE_BATCH takes two launches a step, a workgroup per slice for
+// the gradients and one for Adam (4096 points 107 us, 631 on one workgroup; 20,000 363,
+// 3070).
+struct TrainWaveLds {
+  float h1[32 * H1S];                 // h1[c][k]
+  float dz[64 * DZS];                 // dz2^T[j][c], later dz1^T[k][c]
+  float dh[64 * DZS];                 // dv_c h2[j][c]
+  float xy[32][2];
+};
+
+constexpr int TW = 4;                 // waves per workgroup
+constexpr size_t waves_lds_bytes() { return PARAM_PAD * sizeof(float) + TW * sizeof(TrainWaveLds); }
+constexpr int OWN = (MLP_PARAMS + TW * 64 - 1) / (TW * 64);   // parameters per thread in Adam
+constexpr int GSTRIDE = GPAD;                                  // one wave's gradient slice (+ loss)
+static_assert(TW * GSTRIDE * sizeof(float) <= TW * sizeof(TrainWaveLds), "gradient slices fit the wave buffers");
+
+// `slice` 0: the whole batch.  Else (A.update == 0, A.steps == 1) workgroup g takes the
+// points [g slice, (g + 1) slice) of the batch of order step `order_step` and writes its
+// gradient sum (and loss) to A.grad_out + g GPAD.
+__global__ __launch_bounds__(TW * 64) void k_mlp_train_waves(TrainArgs A, int32_t slice, int32_t order_step) {
+  extern __shared__ float tlds[];
+  float* th = tlds;
+  TrainWaveLds* WL = reinterpret_cast<TrainWaveLds*>(tlds + PARAM_PAD);
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, h = lane >> 5, c = lane & 31;
+  TrainWaveLds& L = WL[w];
+  for (int i = tid; i < MLP_PARAMS; i += TW * 64) th[i] = A.params[i];
+  float mown[OWN], sown[OWN];           // Adam moments of parameters tid + i TW 64
+#pragma unroll
+  for (int i = 0; i < OWN; ++i) {
+    const int q = tid + i * TW * 64;
+    mown[i] = (q < MLP_PARAMS && A.update) ? A.m[q] : 0.0f;
+    sown[i] = (q < MLP_PARAMS && A.update) ? A.s[q] : 0.0f;
+  }
+  __syncthreads();
+  const float inv_b = 1.0f / (float)A.batch;
+  // this workgroup's points of each batch: all of them, or one slice
+  const int pbase = slice > 0 ? (int)blockIdx.x * slice : 0;
+  const int pend = slice > 0 ? min(A.batch, pbase + slice) : A.batch;
+  const int rounds = (pend - pbase + 32 * TW - 1) / (32 * TW);
+
+  for (int step = 0; step < A.steps; ++step) {
+    f32x16 gw2[2][2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) gw2[a][b] = f32x16{};
+    float g_b2 = 0.0f, g_w3 = 0.0f, g_w1x = 0.0f, g_w1y = 0.0f, g_b1 = 0.0f, g_b3 = 0.0f, loss = 0.0f;
+
+    for (int rd = 0; rd < rounds; ++rd) {
+      const int p = pbase + rd * 32 * TW + 32 * w + c;
+      const bool inb = p < pend;
+      const int64_t oi = ((int64_t)(step + order_step) * A.batch + p) % A.n_order;
+      const int32_t oidx = inb ? A.order[oi] : -1;
+      const bool valid = oidx >= 0 && (int64_t)oidx < A.n_points;
+      const int32_t idx = valid ? oidx : 0;
+      const float x = valid ? A.xy[2 * (int64_t)idx] : 0.0f;
+      const float y = valid ? A.xy[2 * (int64_t)idx + 1] : 0.0f;
+      const float t = valid ? A.target[idx] : 0.0f;
+      if (h == 0) { L.xy[c][0] = x; L.xy[c][1] = y; }
+      // layer 1: units k = 32 kb + acc_row(r, h) of point c
+      float h1r[2][16];
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int k = 32 * kb + acc_row(r, h);
+          const float v = tanh_f(th[OW1 + 2 * k] * x + th[OW1 + 2 * k + 1] * y + th[OB1 + k]);
+          h1r[kb][r] = v;
+          L.h1[c * H1S + k] = v;
+        }
+      // layer 2: z2^T[j][c], contraction k(s, h) = 32 (s / 16) + acc_row(s % 16, h)
+      f32x16 z[2];
+#pragma unroll
+      for (int jb = 0; jb < 2; ++jb) {
+        z[jb] = f32x16{};
+        const float* wrow = th + OW2 + (32 * jb + c) * MLP_W;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {          // four steps s = 4q .. 4q+3 read four consecutive k
+          const float4 a4 = *reinterpret_cast<const float4*>(wrow + 32 * (q >> 2) + 8 * (q & 3) + 4 * h);
+          const float av[4] = {a4.x, a4.y, a4.z, a4.w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int s2 = 4 * q + e;
+            z[jb] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[e], h1r[s2 >> 4][s2 & 15], z[jb], 0, 0, 0);
+          }
+        }
+      }
+      // output, residual and dz2 (registers: rows j = 32 jb + acc_row(r, h) of column c)
+      float vpart = 0.0f;
+      float dz2r[2][16];
+#pragma unroll
+      for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int j = 32 * jb + acc_row(r, h);
+          const float h2 = tanh_f(z[jb][r] + th[OB2 + j]);
+          vpart += th[OW3 + j] * h2;
+          z[jb][r] = h2;
+          dz2r[jb][r] = (1.0f - h2 * h2) * th[OW3 + j];
+        }
+      const float v = vpart + __shfl_xor(vpart, 32, 64) + th[OB3];
+      const float res = valid ? v - t : 0.0f;
+      const float dv = res * inv_b;
+      if (h == 0) { loss += 0.5f * res * res * inv_b; g_b3 += dv; }
+#pragma unroll
+      for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int j = 32 * jb + acc_row(r, h);
+          dz2r[jb][r] *= dv;
+          L.dz[j * DZS + c] = dz2r[jb][r];
+          L.dh[j * DZS + c] = dv * z[jb][r];
+        }
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      // gb2[j], gw3[j] for j = lane: sums over the 32 points
+      {
+        const float4* dzr = reinterpret_cast<const float4*>(L.dz + lane * DZS);
+        const float4* dhr = reinterpret_cast<const float4*>(L.dh + lane * DZS);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          const float4 a4 = dzr[q], b4 = dhr[q];
+          g_b2 += (a4.x + a4.y) + (a4.z + a4.w);
+          g_w3 += (b4.x + b4.y) + (b4.z + b4.w);
+        }
+      }
+      // gW2[j][k] += sum_c dz2^T[j][c] h1[c][k]; contraction c(s, h) = 16 h + s
+#pragma unroll
+      for (int jb = 0; jb < 2; ++jb) {
+        const float* arow = L.dz + (32 * jb + c) * DZS + 16 * h;
+        float av[16];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float4 a4 = *reinterpret_cast<const float4*>(arow + 4 * q);
+          av[4 * q] = a4.x; av[4 * q + 1] = a4.y; av[4 * q + 2] = a4.z; av[4 * q + 3] = a4.w;
+        }
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int s2 = 0; s2 < 16; ++s2)
+            gw2[jb][kb] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[s2], L.h1[(16 * h + s2) * H1S + 32 * kb + c],
+                                                               gw2[jb][kb], 0, 0, 0);
+      }
+      // backward: dh1^T[k][c] = sum_j W2[j][k] dz2^T[j][c], contraction j(s, h) = 32 (s / 16) + acc_row(s % 16, h)
+      float dz1r[2][16];
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) {
+        f32x16 d = f32x16{};
+#pragma unroll
+        for (int s2 = 0; s2 < 32; ++s2) {
+          const int j = 32 * (s2 >> 4) + acc_row(s2 & 15, h);
+          d = __builtin_amdgcn_mfma_f32_32x32x2f32(th[OW2 + j * MLP_W + 32 * kb + c], dz2r[s2 >> 4][s2 & 15], d, 0, 0, 0);
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) dz1r[kb][r] = d[r] * (1.0f - h1r[kb][r] * h1r[kb][r]);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) L.dz[(32 * kb + acc_row(r, h)) * DZS + c] = dz1r[kb][r];
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      // gW1[k][.], gb1[k] for k = lane: sums over the 32 points
+      {
+        const float4* dzr = reinterpret_cast<const float4*>(L.dz + lane * DZS);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          const float4 a4 = dzr[q];
+          const float av[4] = {a4.x, a4.y, a4.z, a4.w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int cc = 4 * q + e;
+            g_w1x += av[e] * L.xy[cc][0];
+            g_w1y += av[e] * L.xy[cc][1];
+            g_b1 += av[e];
+          }
+        }
+      }
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
+    // loss and gb3 of the wave (lanes with h == 0 hold one point each)
+    for (int off = 32; off > 0; off >>= 1) {
+      loss += __shfl_xor(loss, off, 64);
+      g_b3 += __shfl_xor(g_b3, off, 64);
+    }
+    // the four waves' gradients into four slices of the (now free) wave
+    // buffers, then summed per parameter in wave order (fixed, reproducible)
+    __syncthreads();
+    float* Gw = reinterpret_cast<float*>(WL) + w * GSTRIDE;
+#pragma unroll
+    for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) Gw[OW2 + (32 * jb + acc_row(r, h)) * MLP_W + 32 * kb + c] = gw2[jb][kb][r];
+    Gw[OW1 + 2 * lane] = g_w1x;
+    Gw[OW1 + 2 * lane + 1] = g_w1y;
+    Gw[OB1 + lane] = g_b1;
+    Gw[OB2 + lane] = g_b2;
+    Gw[OW3 + lane] = g_w3;
+    if (lane == 0) { Gw[OB3] = g_b3; Gw[MLP_PARAMS] = loss; }
+    __syncthreads();
+    const float* G0 = reinterpret_cast<const float*>(WL);
+    auto gsum = [&](int q) __attribute__((always_inline)) {
+      return ((G0[q] + G0[GSTRIDE + q]) + G0[2 * GSTRIDE + q]) + G0[3 * GSTRIDE + q];
+    };
+    if (!A.update) {
+      if (slice > 0) {
+        float* out = A.grad_out + (size_t)blockIdx.x * GPAD;
+        for (int q = tid; q <= MLP_PARAMS; q += TW * 64) out[q] = gsum(q);
+        return;
+      }
+      if (tid == 0 && A.losses) A.losses[step] = gsum(MLP_PARAMS);
+      for (int q = tid; q < MLP_PARAMS; q += TW * 64) A.grad_out[q] = gsum(q);
+      return;
+    }
+    if (tid == 0 && A.losses) A.losses[step] = gsum(MLP_PARAMS);
+    // Adam (bias-corrected), beta1 = 0.9, beta2 = 0.999, eps = 1e-8; each
+    // thread keeps the moments of the parameters it owns in registers
+    const int tstep = A.step0 + step + 1;
+    const float c1 = 1.0f - powf(0.9f, (float)tstep);
+    const float c2 = 1.0f - powf(0.999f, (float)tstep);
+#pragma unroll
+    for (int i = 0; i < OWN; ++i) {
+      const int q = tid + i * TW * 64;
+      if (q < MLP_PARAMS) {
+        const float g = gsum(q);
+        const float mq = 0.9f * mown[i] + 0.1f * g;
+        const float sq = 0.999f * sown[i] + 0.001f * g * g;
+        mown[i] = mq;
+        sown[i] = sq;
+        th[q] -= A.lr * (mq / c1) / (sqrtf(sq / c2) + 1e-8f);
+      }
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int i = 0; i < OWN; ++i) {
+    const int q = tid + i * TW * 64;
+    if (q < MLP_PARAMS && A.update) {
+      A.m[q] = mown[i];
+      A.s[q] = sown[i];
+    }
+  }
+  for (int i = tid; i < MLP_PARAMS; i += TW * 64) A.params[i] = th[i];
+}
+
+// The update of a step over slices: their gradients in order, then Adam with the
+// moments in global memory.
+__global__ __launch_bounds__(256) void k_mlp_adam(float* __restrict__ params, float* __restrict__ m,
+                                                  float* __restrict__ s, const float* __restrict__ part, int groups,
+                                                  int tstep, float lr, float* losses) {
+  const float c1 = 1.0f - powf(0.9f, (float)tstep);
+  const float c2 = 1.0f - powf(0.999f, (float)tstep);
+  for (int q = threadIdx.x; q <= MLP_PARAMS; q += 256) {
+    float g = 0.0f;
+    for (int b = 0; b < groups; ++b) g += part[(size_t)b * GPAD + q];
+    if (q == MLP_PARAMS) {
+      if (losses) *losses = g;
+      continue;
+    }
+    const float mq = 0.9f * m[q] + 0.1f * g;
+    const float sq = 0.999f * s[q] + 0.001f * g * g;
+    m[q] = mq;
+    s[q] = sq;
+    params[q] -= lr * (mq / c1) / (sqrtf(sq / c2) + 1e-8f);
+  }
+}
+
 __global__ void k_mlp_zero(uint32_t* flags) { flags[threadIdx.x] = 0u; }
 
 // Glorot-uniform weights, zero biases: parameter i of a weight matrix with
@@ -686,6 +970,57 @@ pdd_status run_mlp_bake(pdd_ctx* ctx, const float* params, const pdd_partition& 
   return check_hip(ctx, hipGetLastError(), "launch mlp_bake");
 }
 
+namespace {
+
+hipError_t waves_lds() {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mlp_train_waves), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)waves_lds_bytes());
+}
+
+pdd_status train_by_waves(pdd_ctx* ctx, const TrainArgs& A) {
+  const hipError_t e = waves_lds();
+  if (e != hipSuccess) return check_hip(ctx, e, "hipFuncSetAttribute(mlp_train)");
+  hipLaunchKernelGGL(k_mlp_train_waves, dim3(1), dim3(TW * 64), waves_lds_bytes(), ctx->stream, A, 0, 0);
+  return check_hip(ctx, hipGetLastError(), "launch mlp_train");
+}
+
+// The slices' gradients of captured calls: allocated by the calls that are not, each
+// at least twice as large as the last, and kept with the context, so that a graph's
+// buffer stays where it is.  Null: there is none of this size.
+float* slice_gradients(pdd_ctx* ctx, size_t bytes, bool captured) {
+  auto& all = ctx->mlp_slices;
+  const size_t have = all.empty() ? 0 : all.back()->bytes;
+  if (bytes > have) {
+    if (captured) return nullptr;
+    auto fresh = std::make_unique<DeviceBuffer>();
+    if (fresh->reserve(std::max(bytes, 2 * have)) != hipSuccess) {
+      (void)hipGetLastError();                      // no room: a captured call takes one workgroup
+      return nullptr;
+    }
+    all.push_back(std::move(fresh));
+  }
+  return all.back()->as<float>();
+}
+
+pdd_status train_by_slices(pdd_ctx* ctx, TrainArgs A, int32_t slices, float* grads) {
+  const hipError_t e = waves_lds();
+  if (e != hipSuccess) return check_hip(ctx, e, "hipFuncSetAttribute(mlp_train)");
+  const int32_t steps = A.steps;
+  float* losses = A.losses;
+  A.update = 0;
+  A.steps = 1;
+  A.losses = nullptr;
+  A.grad_out = grads;
+  for (int32_t st = 0; st < steps; ++st) {
+    hipLaunchKernelGGL(k_mlp_train_waves, dim3(slices), dim3(TW * 64), waves_lds_bytes(), ctx->stream, A, WIDE_SLICE, st);
+    hipLaunchKernelGGL(k_mlp_adam, dim3(1), dim3(256), 0, ctx->stream, A.params, A.m, A.s, A.grad_out, slices,
+                       A.step0 + st + 1, A.lr, losses ? losses + st : nullptr);
+  }
+  return check_hip(ctx, hipGetLastError(), "launch mlp_train (slices)");
+}
+
+}  // namespace
+
 pdd_status run_mlp_train(pdd_ctx* ctx, float* params, float* m, float* s, int64_t n_points, const float* xy,
                          const float* target, const int32_t* order, int64_t n_order, int32_t batch, int32_t steps,
                          int32_t step0, float lr, float* losses, float* grad_out) {
@@ -704,11 +1039,15 @@ pdd_status run_mlp_train(pdd_ctx* ctx, float* params, float* m, float* s, int64_
   // with a slice for every workgroup whole slices keep them as busy, at a quarter of the gradients to exchange
   const bool whole = slices >= TRAIN_G;
   int G = (int)std::min<int64_t>({(int64_t)A.units, (int64_t)TRAIN_G, (int64_t)ctx->cu_count});
-  // a captured call runs on one workgroup: no scratch, no cooperative launch
+  // a captured call, and one step of at most a round of four units: see k_mlp_train_waves
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(ctx->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusActive) G = 1;
-  // one step of two units: a cooperative launch costs more than the second CU gives (43 us against 39)
-  if (steps == 1 && A.units <= 2) G = 1;
+  const bool captured = hipStreamIsCapturing(ctx->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusActive;
+  if (slices > 1) {
+    float* grads = slice_gradients(ctx, (size_t)slices * GPAD * sizeof(float), captured);
+    if (captured && grads) return train_by_slices(ctx, A, (int32_t)slices, grads);
+  }
+  if (slices == 1 && A.units > 1 && (captured || (steps == 1 && batch <= 128))) return train_by_waves(ctx, A);
+  if (captured) G = 1;
   const void* f = slices == 1 ? reinterpret_cast<const void*>(&k_mlp_train<ONE>)
                   : whole     ? reinterpret_cast<const void*>(&k_mlp_train<WHOLE>)
                               : reinterpret_cast<const void*>(&k_mlp_train<UNITS>);
