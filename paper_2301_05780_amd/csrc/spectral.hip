@@ -307,19 +307,31 @@ __device__ __forceinline__ double bary_basis(const double* nodes, const double* 
   return r / wave_sum(r);
 }
 
+// Node `i` of n in [lo, hi]: its coordinate and its square of H (side S), as
+// for any point (monotone in i, so a square owns a range of nodes).
+__device__ __forceinline__ double node_at(double lo, double hi, int i, int n) {
+  return lo + (hi - lo) * (double)i / (double)(n - 1);
+}
+__device__ __forceinline__ int square_of(double x, double lo, double S, int H) {
+  return min(max((int)floor((x - lo) / S), 0), H - 1);
+}
+
 // One wave per point: 2-D barycentric interpolation of u, du/dx, du/dy on the
-// point's square (outputs u[n], grad[2 n], each nullable).
+// point's square.  Points are either xy[2 n] (outputs u[n], grad[2 n], each
+// nullable) or, with lut_n > 0, the lut_n^2 nodes of the domain's node grid
+// (output grad_lut[(j lut_n + i) 2 + d] in float32).
 __global__ __launch_bounds__(256) void k_spec_eval(SpecDev T, int32_t p, int32_t H, double x0, double x1, double y0,
                                                    double y1, const double* __restrict__ grid, int64_t n_pts,
-                                                   const double* __restrict__ xy, double* u, double* grad) {
+                                                   const double* __restrict__ xy, int32_t lut_n, double* u,
+                                                   double* grad, float* grad_lut) {
   __shared__ double lys[4][64];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int N = p + 1;
   const double Sx = (x1 - x0) / H, Sy = (y1 - y0) / H;
   for (int64_t q = (int64_t)blockIdx.x * 4 + wv; q < n_pts; q += (int64_t)gridDim.x * 4) {
-    const double x = xy[2 * q], y = xy[2 * q + 1];
-    const int a = min(max((int)floor((x - x0) / Sx), 0), H - 1);
-    const int c = min(max((int)floor((y - y0) / Sy), 0), H - 1);
+    const double x = lut_n > 0 ? node_at(x0, x1, (int)(q % lut_n), lut_n) : xy[2 * q];
+    const double y = lut_n > 0 ? node_at(y0, y1, (int)(q / lut_n), lut_n) : xy[2 * q + 1];
+    const int a = square_of(x, x0, Sx, H), c = square_of(y, y0, Sy, H);
     const double zx = 2.0 * (x - (x0 + a * Sx)) / Sx - 1.0;
     const double zy = 2.0 * (y - (y0 + c * Sy)) / Sy - 1.0;
     const double lx = bary_basis(T.nodes, T.bw, p, zx);
@@ -346,6 +358,10 @@ __global__ __launch_bounds__(256) void k_spec_eval(SpecDev T, int32_t p, int32_t
         grad[2 * q] = out[1];
         grad[2 * q + 1] = out[2];
       }
+      if (grad_lut) {
+        grad_lut[2 * q] = (float)out[1];
+        grad_lut[2 * q + 1] = (float)out[2];
+      }
     }
   }
 }
@@ -362,17 +378,11 @@ __global__ __launch_bounds__(256) void k_spec_eval(SpecDev T, int32_t p, int32_t
 // l / 16 + 4 q of the K step (tile, q), are the second product's B operand
 // with the contraction taken in that order.  A 1025^2 table over 100 squares
 // at p = 63 takes 42 us (one wave and two 64-lane sums per node: 10.8 ms);
-// what remains is the basis divisions and the last, partly filled tiles.
+// what remains is the basis divisions and the last, partly filled tiles.  Tiles and
+// K steps go up to the grid's size (p = 8, 65 nodes, 4 squares: 18.4 us at 64 grid
+// points, now 7.4), and tables of few nodes keep k_spec_eval, see few_nodes.
 constexpr int TAB = 64;             // nodes per workgroup and direction
 
-// Node `i` of n in [lo, hi]: its coordinate and its square of H (side S), as
-// for any point (monotone in i, so a square owns a range of nodes).
-__device__ __forceinline__ double node_at(double lo, double hi, int i, int n) {
-  return lo + (hi - lo) * (double)i / (double)(n - 1);
-}
-__device__ __forceinline__ int square_of(double x, double lo, double S, int H) {
-  return min(max((int)floor((x - lo) / S), 0), H - 1);
-}
 // first node whose square is at least a (n for a = H)
 __device__ __forceinline__ int first_node(double lo, double hi, double S, int H, int n, int a) {
   if (a <= 0) return 0;
@@ -387,11 +397,12 @@ __device__ __forceinline__ int first_node(double lo, double hi, double S, int H,
 // of equal l % 16: this lane's values at the grid points 4 s + l / 16.
 // *hit: the grid point that z equals exactly (the basis is then that unit
 // vector), or -1.
-__device__ __forceinline__ void bary_frag(const SpecDev& T, int N, int kq, double z, double (&b)[16], int* hit) {
+template <int K>
+__device__ __forceinline__ void bary_frag(const SpecDev& T, int N, int kq, double z, double (&b)[K], int* hit) {
   int at = -1;
   double sum = 0.0;
 #pragma unroll
-  for (int s = 0; s < 16; ++s) {
+  for (int s = 0; s < K; ++s) {
     const int k = 4 * s + kq;
     double r = 0.0;
     if (k < N) {
@@ -407,10 +418,12 @@ __device__ __forceinline__ void bary_frag(const SpecDev& T, int N, int kq, doubl
   sum += __shfl_xor(sum, 16, 64);
   sum += __shfl_xor(sum, 32, 64);
 #pragma unroll
-  for (int s = 0; s < 16; ++s) b[s] = at >= 0 ? (4 * s + kq == at ? 1.0 : 0.0) : b[s] / sum;
+  for (int s = 0; s < K; ++s) b[s] = at >= 0 ? (4 * s + kq == at ? 1.0 : 0.0) : b[s] / sum;
   *hit = at;
 }
 
+// NT: sixteens of grid points per direction, (p + 16) / 16.
+template <int NT>
 __global__ __launch_bounds__(256) void k_spec_table(SpecDev T, int32_t p, int32_t H, double x0, double x1, double y0,
                                                     double y1, const double* __restrict__ grid, int32_t lut_n,
                                                     int32_t tiles, float* __restrict__ out) {
@@ -430,14 +443,15 @@ __global__ __launch_bounds__(256) void k_spec_table(SpecDev T, int32_t p, int32_
   const int ni = min(TAB, first_node(x0, x1, Sx, H, lut_n, a + 1) - i0);
   const int nj = min(TAB, first_node(y0, y1, Sy, H, lut_n, c + 1) - j0);
   if (ni <= 0 || nj <= 0) return;                  // uniform: an edge tile that holds no node
-  double b[16];
+  constexpr int K = 4 * NT;                        // K steps of four grid points
+  double b[K];
   int hit;
   // the strip w of the y nodes, into LDS
   if (16 * w < nj) {
     const double y = node_at(y0, y1, j0 + min(16 * w + r, nj - 1), lut_n);
     bary_frag(T, N, kq, 2.0 * (y - (y0 + c * Sy)) / Sy - 1.0, b, &hit);
 #pragma unroll
-    for (int s = 0; s < 16; ++s) By[(16 * w + r) * LDT + 4 * s + kq] = b[s];
+    for (int s = 0; s < K; ++s) By[(16 * w + r) * LDT + 4 * s + kq] = b[s];
   }
   __syncthreads();
   if (16 * w >= ni) return;                        // no barrier follows
@@ -447,21 +461,21 @@ __global__ __launch_bounds__(256) void k_spec_table(SpecDev T, int32_t p, int32_
 #pragma unroll
   for (int d = 0; d < 2; ++d) {
     const double* G = grid + ((size_t)(a + (int64_t)H * c) * 3 + 1 + d) * (size_t)N * N;
-    v4d M[4];
+    v4d M[NT];
 #pragma unroll
-    for (int rt = 0; rt < 4; ++rt) {
+    for (int rt = 0; rt < NT; ++rt) {
       M[rt] = v4d{0.0, 0.0, 0.0, 0.0};
       const int l = 16 * rt + r;
-      double g[16];
+      double g[K];
 #pragma unroll
-      for (int s = 0; s < 16; ++s) g[s] = (l < N && 4 * s + kq < N) ? G[(size_t)(4 * s + kq) * N + l] : 0.0;
+      for (int s = 0; s < K; ++s) g[s] = (l < N && 4 * s + kq < N) ? G[(size_t)(4 * s + kq) * N + l] : 0.0;
 #pragma unroll
-      for (int s = 0; s < 16; ++s) M[rt] = __builtin_amdgcn_mfma_f64_16x16x4f64(g[s], b[s], M[rt], 0, 0, 0);
+      for (int s = 0; s < K; ++s) M[rt] = __builtin_amdgcn_mfma_f64_16x16x4f64(g[s], b[s], M[rt], 0, 0, 0);
     }
     // a node on a grid column takes that column's values alone
     if (hit >= 0) {
 #pragma unroll
-      for (int rt = 0; rt < 4; ++rt)
+      for (int rt = 0; rt < NT; ++rt)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int l = 16 * rt + kq + 4 * q;
@@ -473,7 +487,7 @@ __global__ __launch_bounds__(256) void k_spec_table(SpecDev T, int32_t p, int32_
       o[d][jt] = v4d{0.0, 0.0, 0.0, 0.0};
       if (16 * jt < nj) {
 #pragma unroll
-        for (int rt = 0; rt < 4; ++rt)
+        for (int rt = 0; rt < NT; ++rt)
 #pragma unroll
           for (int q = 0; q < 4; ++q)
             o[d][jt] = __builtin_amdgcn_mfma_f64_16x16x4f64(By[(16 * jt + r) * LDT + 16 * rt + 4 * q + kq], M[rt][q],
@@ -556,19 +570,41 @@ hipError_t launch_spectral_eval(const SpecDev& T, int32_t p, int32_t H, double x
                                 hipStream_t stream) {
   const unsigned blocks = (unsigned)std::min<int64_t>((n_pts + 3) / 4, 65536);
   hipLaunchKernelGGL(k_spec_eval, dim3(std::max(blocks, 1u)), dim3(256), 0, stream, T, p, H, x0, x1, y0, y1, grid, n_pts,
-                     xy, u, grad);
+                     xy, 0, u, grad, nullptr);
   return hipGetLastError();
 }
 
+// A wave per node, all resident at once, against a chain of bases and two products
+// in a workgroup per square, of which some thousand run at once.  us, node by node
+// and by squares: 17^2 nodes 6.2 and 7.7 (p = 3, 64 squares), 6.2 and 11.2 (p = 31);
+// 65^2 7.7 and 8.2 (p = 8, 64), 9.4 and 10.5 (p = 16, 16), 14.6 and 15.0 (p = 32, 256), 6.8
+// and 39 (p = 8, 4096); 101^2 11.7 and 7.4 (p = 2, 4), 12.8 and 40 (p = 8, 4096); 200^2
+// 35 and 39 (p = 2, 4096).
+bool few_nodes(int32_t p, int32_t H, int64_t lut_n) { return lut_n * lut_n * (p + 9) < 65536 + (int64_t)128 * H * H; }
+
 hipError_t launch_spectral_table(const SpecDev& T, int32_t p, int32_t H, double x0, double x1, double y0, double y1,
                                  const double* grid, int32_t lut_n, float* grad_lut, hipStream_t stream) {
+  if (few_nodes(p, H, lut_n)) {
+    const int64_t nodes = (int64_t)lut_n * lut_n;
+    hipLaunchKernelGGL(k_spec_eval, dim3((unsigned)std::min<int64_t>((nodes + 3) / 4, 65536)), dim3(256), 0, stream, T, p,
+                       H, x0, x1, y0, y1, grid, nodes, nullptr, lut_n, nullptr, nullptr, grad_lut);
+    return hipGetLastError();
+  }
   // a square holds at most (lut_n - 1) / H + 2 nodes per direction
   const int64_t tiles = ((lut_n - 1) / H + 2 + TAB - 1) / TAB;
   const int64_t blocks = (int64_t)H * H * tiles * tiles;
   if (blocks > INT32_MAX) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_spec_table, dim3((unsigned)blocks), dim3(256), 0, stream, T, p, H, x0, x1, y0, y1, grid, lut_n,
-                     (int32_t)tiles, grad_lut);
-  return hipGetLastError();
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, stream, T, p, H, x0, x1, y0, y1, grid, lut_n,
+                       (int32_t)tiles, grad_lut);
+    return hipGetLastError();
+  };
+  switch ((p + 16) / 16) {
+    case 1: return launch(k_spec_table<1>);
+    case 2: return launch(k_spec_table<2>);
+    case 3: return launch(k_spec_table<3>);
+    default: return launch(k_spec_table<4>);
+  }
 }
 
 hipError_t launch_lut_field_range(const float* lut, int64_t nodes, double* out, hipStream_t stream) {

@@ -227,3 +227,12 @@ def test_gradient_table_tiles(ctx, H, p, n):
     got = tab.cpu().numpy()
     assert np.max(np.abs(got - ref)) <= (2.0 ** -23 + 1e-13 * (p + 1)) * scale
     assert np.max(np.abs(got.reshape(-1, 2)[few] - np.stack(orc[1:], axis=1))) <= (2.0 ** -23 + 1e-12 * (p + 1)) * scale
+
+
+@pytest.mark.parametrize("H,p,n", [(2, 15, 150), (2, 16, 150), (3, 31, 97), (3, 32, 97), (2, 47, 70), (2, 48, 70),
+                                   (16, 15, 101), (5, 7, 64), (5, 7, 65), (64, 3, 220), (64, 3, 17)])
+def test_gradient_table_sizes(ctx, H, p, n):
+    """As above at the edges of the grid points' sixteens (p + 1 = 16, 17, ..., 49),
+    with many squares of few nodes, and on both sides of the rule for tables of few
+    nodes, which are interpolated node by node."""
+    test_gradient_table_tiles(ctx, H, p, n)
