@@ -134,8 +134,9 @@ __global__ __launch_bounds__(BLK) void k_eval(EvalArgs A) {
   const int lane = threadIdx.x & 63;
   const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int64_t wave = (int64_t)blockIdx.x * (BLK / 64) + wid;
-  const int64_t pt = wave / A.waves_per_pt;
-  const int64_t part = wave - pt * A.waves_per_pt;
+  // (several waves per point: few points, and the wave's number has 32 bits)
+  const bool split = A.waves_per_pt > 1;
+  const int64_t pt = split ? (int64_t)((uint32_t)wave / (uint32_t)A.waves_per_pt) : wave;
   if (pt >= A.n_pts) return;
   const double px = A.xy[2 * pt], py = A.xy[2 * pt + 1];
   if (!(px >= P.x0 && px <= P.x1 && py >= P.y0 && py <= P.y1)) {
@@ -180,28 +181,53 @@ __global__ __launch_bounds__(BLK) void k_eval(EvalArgs A) {
   uint32_t* Qf = queue_fl[wid];
   int qn = 0;                            // queued exits
   // this wave's range of the point's paths
-  uint32_t next = (uint32_t)(A.n_paths * part / A.waves_per_pt);
-  const uint32_t end = (uint32_t)(A.n_paths * (part + 1) / A.waves_per_pt);
+  uint32_t next = 0, end = (uint32_t)A.n_paths;
+  if (split) {
+    const int64_t part = wave - pt * A.waves_per_pt;
+    next = (uint32_t)(A.n_paths * part / A.waves_per_pt);
+    end = (uint32_t)(A.n_paths * (part + 1) / A.waves_per_pt);
+  }
+  // the score of a path that ended at (x, y) with the sides `fl` flagged
+  auto score = [&](R x, R y, R Y, R Z, uint32_t fl) __attribute__((always_inline)) {
+    const int o = choose_side<R>(x, y, fl & 1u, (fl >> 1) & 1u, (fl >> 2) & 1u, (fl >> 3) & 1u, d.line);
+    const bool vert = (o == 0 || o == 2);
+    R s;
+    if (isnan(x) || isnan(y)) {
+      s = (R)NAN;
+    } else {
+      const R val = line_value<KIND, R, F64>(A, d, o, vert ? y : x);
+      {
+#pragma clang fp contract(off)
+        s = Z + Y * val;
+      }
+    }
+    s1 += (double)s;
+    s2 += (double)s * (double)s;
+  };
+  // draw j of path p, up to two steps: the flagged sides (0: goes on)
+  auto step_pair = [&](uint32_t p, uint32_t& j, R& x, R& y, R& Y, R& Z) __attribute__((always_inline)) -> uint32_t {
+    const U4 r = philox10(j, p, (uint32_t)pt, A.inst, P.key0, P.key1);
+    R z0, z1;
+    if constexpr (F64) box_muller(uniform64(r.a), uniform64(r.b), z0, z1);
+    else box_muller(uniform32(r.a), uniform32(r.b), z0, z1);
+    em_step<KIND, R>(P.coef, h, sq, z0, z1, x, y, Y, Z);
+    uint32_t fl = exit_sides<KIND, R>(P.coef, P.exit_rule, sq, d.line, e, x, y);
+    if (fl == 0) {
+      if constexpr (F64) box_muller(uniform64(r.c), uniform64(r.d), z0, z1);
+      else box_muller(uniform32(r.c), uniform32(r.d), z0, z1);
+      em_step<KIND, R>(P.coef, h, sq, z0, z1, x, y, Y, Z);
+      fl = exit_sides<KIND, R>(P.coef, P.exit_rule, sq, d.line, e, x, y);
+    }
+    ++j;
+    if (fl == 0 && 2 * j >= MAX_STEPS) fl = 15u;
+    return fl;
+  };
   auto resolve = [&]() __attribute__((always_inline)) {
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     __builtin_amdgcn_wave_barrier();
     for (int i = lane; i < qn; i += 64) {
       const EvalExit<R> r = Q[i];
-      const uint32_t fl = Qf[i];
-      const int o = choose_side<R>(r.x, r.y, fl & 1u, (fl >> 1) & 1u, (fl >> 2) & 1u, (fl >> 3) & 1u, d.line);
-      const bool vert = (o == 0 || o == 2);
-      R s;
-      if (isnan(r.x) || isnan(r.y)) {
-        s = (R)NAN;
-      } else {
-        const R val = line_value<KIND, R, F64>(A, d, o, vert ? r.y : r.x);
-        {
-#pragma clang fp contract(off)
-          s = r.Z + r.Y * val;
-        }
-      }
-      s1 += (double)s;
-      s2 += (double)s * (double)s;
+      score(r.x, r.y, r.Y, r.Z, Qf[i]);
     }
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -210,6 +236,17 @@ __global__ __launch_bounds__(BLK) void k_eval(EvalArgs A) {
   bool active = false;
   R x = 0, y = 0, Y = 0, Z = 0;
   uint32_t p = 0, j = 0;
+  // A path per lane: nothing to refill or to wait for, and the queue would only cost
+  // (1000 points of 64 paths: 43 us, 55 with it)
+  if (end - next <= 64u) {
+    if (next + lane < end) {
+      x = (R)px; y = (R)py; Y = (R)1;
+      uint32_t fl = 0;
+      while (fl == 0) fl = step_pair(next + lane, j, x, y, Y, Z);
+      score(x, y, Y, Z, fl);
+    }
+    next = end;
+  }
   while (true) {
     const uint64_t idle = __ballot(!active);
     const int n_idle = __popcll(idle);
@@ -227,22 +264,7 @@ __global__ __launch_bounds__(BLK) void k_eval(EvalArgs A) {
       break;                             // every path handed out and ended
     }
     uint32_t fl = 0;
-    if (active) {
-      const U4 r = philox10(j, p, (uint32_t)pt, A.inst, P.key0, P.key1);
-      R z0, z1;
-      if constexpr (F64) box_muller(uniform64(r.a), uniform64(r.b), z0, z1);
-      else box_muller(uniform32(r.a), uniform32(r.b), z0, z1);
-      em_step<KIND, R>(P.coef, h, sq, z0, z1, x, y, Y, Z);
-      fl = exit_sides<KIND, R>(P.coef, P.exit_rule, sq, d.line, e, x, y);
-      if (fl == 0) {
-        if constexpr (F64) box_muller(uniform64(r.c), uniform64(r.d), z0, z1);
-        else box_muller(uniform32(r.c), uniform32(r.d), z0, z1);
-        em_step<KIND, R>(P.coef, h, sq, z0, z1, x, y, Y, Z);
-        fl = exit_sides<KIND, R>(P.coef, P.exit_rule, sq, d.line, e, x, y);
-      }
-      ++j;
-      if (fl == 0 && 2 * j >= MAX_STEPS) fl = 15u;
-    }
+    if (active) fl = step_pair(p, j, x, y, Y, Z);
     const uint64_t em = __ballot(fl != 0);
     if (em != 0) {
       if (fl != 0) {
@@ -287,13 +309,15 @@ __global__ __launch_bounds__(BLK) void k_eval_sum(EvalArgs A) {
 }
 
 // Waves per point: enough waves to fill the device (EVAL_WAVES, six per SIMD),
-// each with at least 64 paths.  More, shorter ranges idle more lanes while a
+// each with about 64 paths at least; fewer than 128 stay together, as half-empty
+// waves and the second kernel cost more than they give (5000 points of 80 paths, 4
+// steps: 44 us in two waves each, 35 in one; 3000 of 65 34, 27).  More, shorter ranges idle more lanes while a
 // range's last paths end; fewer leave SIMDs without work: 4096, 6144, 8192 and
 // 12288 waves take 0.375, 0.41, 0.42 and 0.51 ms for 50 points of 20,000
 // paths, and 0.241, 0.232, 0.229 and 0.229 ms for 1000 points of 4000.
 constexpr int64_t EVAL_WAVES = 6144;
 int32_t eval_split(int64_t n_pts, int64_t n_paths) {
-  const int64_t fill = (EVAL_WAVES + n_pts - 1) / n_pts, most = (n_paths + 63) / 64;
+  const int64_t fill = (EVAL_WAVES + n_pts - 1) / n_pts, most = n_paths < 128 ? 1 : (n_paths + 63) / 64;
   return (int32_t)std::max<int64_t>(1, std::min(fill, most));
 }
 

@@ -162,3 +162,27 @@ def test_eval_on_two_streams_in_turn(ctx):
                 assert torch.equal(a, b)
     finally:
         ctx.check(pdd.lib().pdd_set_stream(ctx.h, ctx.stream.cuda_stream))
+
+
+@pytest.mark.parametrize("n_pts,n_paths", [(1, 127), (2, 128), (5000, 80), (6143, 65), (8300, 63), (8200, 3)])
+def test_eval_at_the_last_points_too(ctx, n_pts, n_paths):
+    """Ranges of at most 64 paths run a path per lane, and fewer than 128 paths stay
+    in one wave: float64 values against the oracle (1e-12 as above) at points over
+    the whole call, the first and the last among them."""
+    w = dict(kind="varcoef", param=(), domain=(0.0, 1.0, 0.0, 1.0), H=4, m=8, ext=4, n_paths=1, h=2e-3, seed=6,
+             precision="fp64", exit_rule="gm", instance=0)
+    g = Geometry(w["domain"], w["H"], w["m"], w["ext"])
+    rng = np.random.default_rng(n_pts)
+    uk = rng.uniform(-1.0, 1.0, g.n)
+    pts = rng.uniform(0.0, 1.0, size=(n_pts, 2))
+    u, se = ctx.eval_subdomain(w, torch.from_numpy(uk).cuda(), torch.from_numpy(pts).cuda(), n_paths)
+    ctx.sync()
+    u, se = u.cpu().numpy(), se.cpu().numpy()
+    keep = np.unique(np.append(rng.integers(0, n_pts, size=12), [0, n_pts - 1]))
+    inside = np.full_like(pts, 0.5)      # a crossing of grid lines: no paths, and the others keep their stream words
+    inside[keep] = pts[keep]
+    ref_u, ref_se, _ = evaluate(g, Coefficients("varcoef"), uk, inside, n_paths, w["h"], w["seed"], instance=0,
+                                exit_rule="gm")
+    assert np.all(np.abs(u[keep] - ref_u[keep]) <= 1e-12 * (1.0 + np.abs(ref_u[keep])))
+    assert np.allclose(se[keep], ref_se[keep], rtol=1e-9, atol=1e-7)
+    assert np.isfinite(u).all() and np.isfinite(se).all()
