@@ -269,20 +269,19 @@ inline int64_t solo_ticket(int64_t paths, int64_t waves) {
 // lane) and no more than 1.7 tickets per wave.  29 knots of 1000 float64 paths:
 // 1.02 ms with 256, 0.64 ms with 64; 369 knots of 1000: 0.92, 0.69 ms; 369 of 4000:
 // 1.20, 0.99 ms; 1729 of 1000: 2.01, 1.82 ms.
-//   Large runs with equal counts: 5.65 tickets per wave at most, so that the
-// last third of the waves, which a SIMD serves last, has one ticket less than the
-// others.  1729 knots of 10,000 paths on 6144 waves: 5.63 tickets per wave 1.03 ms,
-// 5.06 1.10, 5.91 1.17, 6.75 1.13, 7.04 1.12; shorter tickets than 256 cost more.
+// Over 238 runs (10 geometries, 8 to 100 steps, equal and unequal counts) 256 over this
+// cut: 0.88 to 1.51, 1.05 to 1.2 on average from 1.25 tickets of 256 per wave down to 0.15.
+//   Large runs: per_wave tickets' worth of paths per wave; shorter tickets than 256 cost
+// more.  No other number of them is better in general: of 1729 knots of 10,000 paths the
+// times for 4.5 to 8.7 tickets per wave lie between 1.03 ms (5.63) and 1.16 (5.91, 8.16),
+// 7.04 1.11, and where the short ones lie changes with the paths per knot (2625 knots,
+// 5.64 against 7.18: 0.952 and 0.910 ms for 5000 paths, 1.047 and 1.129 for 6000).
 inline int64_t strided_ticket(int64_t paths, int64_t waves, int64_t knots, int64_t each, int64_t per_wave) {
   if ((double)paths < 1.3 * 256.0 * (double)waves) {
     const double most = 1.7 * (double)waves;
     const int64_t cuts = each > 0 ? (int64_t)(most / (double)knots) : 0;
     const int64_t p = cuts > 0 ? (each + cuts - 1) / cuts : (int64_t)std::ceil((double)paths / most);
     return std::min<int64_t>(256, std::max<int64_t>(64, p));
-  }
-  if (each > 0 && per_wave <= 7) {
-    const int64_t cuts = (int64_t)(5.65 * (double)waves / (double)knots);
-    if (cuts >= 4 && each >= 256 * cuts) return (each + cuts - 1) / cuts;
   }
   return std::max<int64_t>(256, (paths + per_wave * waves - 1) / (per_wave * waves));
 }
