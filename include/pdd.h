@@ -451,9 +451,10 @@ pdd_status pdd_spectral_tables(int32_t p, double* decomp_residual, double* inver
  * stats: device double[n * PDD_CAL_WIDTH], the per-knot sums listed at
  * PDD_CAL_WIDTH, each summed over the knot's paths in a fixed order.  Needs
  * n * n_paths * 40 bytes (plus 512) of scratch, at most 16 GiB, and for many
- * long float32 paths with a gradient table 32 bytes per cell of the table,
- * without which (no memory, or new to a capture) it reads the table as it is:
- * the same bits.  */
+ * long float32 paths with a gradient table 32 bytes per cell of the table (of
+ * tables up to 11,585 nodes a direction, so at most 4.3 GB; it stays with the
+ * context like the rest), without which (no memory, or new to a capture) it reads
+ * the table as it is: the same bits. */
 pdd_status pdd_calibrate(pdd_ctx* ctx, const pdd_coeffs* coeffs, const pdd_partition* part, const pdd_knots* knots,
                          const pdd_run* run, const double* u_knots, double* stats);
 

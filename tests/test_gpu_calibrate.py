@@ -219,3 +219,38 @@ def test_path_without_a_gm_exit(ctx, precision):
         scale = w["n_paths"] * (1.0 + abs(r[1]) / w["n_paths"] + abs(r[3]) / w["n_paths"]) ** 2
         assert np.all(np.abs(runs[0][k, :6] - r[:6]) <= 1e-11 * scale), k
         assert np.array_equal(runs[0][k, 6:], r[6:]), k
+
+
+@pytest.mark.parametrize("kind", ["varcoef", "eq43"])
+def test_cells_and_table_give_the_same_bits(ctx, kind):
+    """The gradient table cell by cell (an ordinary call with many long paths) against
+    the table as it is: a captured call on a context whose scratch an earlier call
+    without a variate has sized, so that there is no room for the cells.  All eight
+    sums, bit for bit, and each replay of the graph."""
+    side = 200.0 if kind == "eq43" else 1.0
+    lo = -100.0 if kind == "eq43" else 0.0
+    w = dict(kind=kind, param=(), domain=(lo, lo + side, lo, lo + side), H=4, m=8, ext=0, n_paths=22700,
+             h=side * side / 16 / 320, seed=14, precision="fp32", exit_rule="gm")
+    n = pdd.pattern(w)[0]
+    assert n * w["n_paths"] >= 4000000
+    u0 = torch.linspace(-1.0, 1.0, n, dtype=torch.float64, device="cuda")
+    spec = pdd.CVSpec("grad_lut", table=torch.from_numpy(_table(9, 97)).cuda())
+    cells = ctx.calibrate(w, u0, w["n_paths"], cv=spec)
+    other = pdd.Context(0)
+    try:
+        other.calibrate(w, u0, w["n_paths"])
+        torch.cuda.synchronize()
+        graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+        with torch.cuda.graph(graph, stream=stream):
+            other.check(pdd.lib().pdd_set_stream(other.h, stream.cuda_stream))
+            rows = other.calibrate(w, u0, w["n_paths"], cv=spec)
+        for _ in range(3):
+            rows.fill_(7.0)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(rows, cells)
+        assert torch.isfinite(cells).all() and (cells[:, 4] > 0).all()
+    finally:
+        torch.cuda.synchronize()
+        other.close()
