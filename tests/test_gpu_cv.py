@@ -8,7 +8,9 @@ from paper_2301_05780_amd import pdd, workloads, cv as cvmod
 from oracle import mlp as omlp
 from oracle.geometry import Geometry
 from oracle.coeffs import Coefficients
-from oracle.assemble import assemble as oracle_assemble, to_csr
+from oracle.assemble import assemble as oracle_assemble, exit_flags_box, to_csr
+from oracle.calibrate import path_scores
+from oracle.philox import philox4x32_10, seed_key
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -642,3 +644,89 @@ def test_gradient_goes_on_alone_when_a_wait_runs_out(ctx, n):
     ctx.sync()
     assert torch.equal(g, g0) and torch.equal(loss, loss0) and torch.equal(p, before)
     assert torch.isfinite(g).all()
+
+
+def _walk(g, c, k, paths, w, points):
+    """The paths of knot k as the collection draws them, in float64 from its 23-bit
+    uniforms: K, the iterates X_n, Y_n, Z_n of the first `points` steps, the value
+    carried out of the patch for u0 = u*, and whether every decision on the way
+    (exits, side) is clear of float32's error."""
+    key = seed_key(w["seed"])
+    idx = np.arange(paths)
+    X = np.full((paths, points, 2), np.nan)
+    YZ = np.full((paths, points, 2), np.nan)
+    x, y = np.full(paths, g.x[k]), np.full(paths, g.y[k])
+    Y, Z = np.ones(paths), np.zeros(paths)
+    K = np.zeros(paths, dtype=int)
+    flags = np.zeros((paths, 4), dtype=bool)
+    clear = np.ones(paths, dtype=bool)
+    alive = np.ones(paths, dtype=bool)
+    box, h, sq = g.box[k], w["h"], np.sqrt(w["h"])
+    n = 0
+    while alive.any():
+        if n % 2 == 0:
+            r = philox4x32_10(n // 2, idx, k, pdd.COLLECT_STREAM, *key)
+            u = [((v >> np.uint64(9)).astype(np.float64) * 2.0 + 1.0) * 2.0 ** -24 for v in r]
+        u0, u1 = u[2 * (n % 2)], u[2 * (n % 2) + 1]
+        rho = np.sqrt(-2.0 * np.log(u0))
+        dWx, dWy = sq * rho * np.cos(2 * np.pi * u1), sq * rho * np.sin(2 * np.pi * u1)
+        if n < points:
+            X[alive, n] = np.stack([x, y], axis=1)[alive]
+            YZ[alive, n] = np.stack([Y, Z], axis=1)[alive]
+        sxx, sxy, syy = c.sigma(x, y)
+        ddx, ddy = c.drift(x, y)
+        cr, fs = c.reaction(x, y), c.source(x, y)
+        nx, ny = x + ddx * h + sxx * dWx + sxy * dWy, y + ddy * h + sxy * dWx + syy * dWy
+        x, y = np.where(alive, nx, x), np.where(alive, ny, y)
+        Z = np.where(alive, Z - fs * Y * h, Z)
+        Y = np.where(alive, Y * (1.0 + cr * h), Y)
+        n += 1
+        far, near = 3e-4, -3e-4
+        grown, shrunk = [np.array(exit_flags_box(c, (box[0] - d, box[1] + d, box[2] - d, box[3] + d), x, y, h, "gm"))
+                         for d in (far, near)]
+        clear &= ~alive | (grown == shrunk).all(axis=0)
+        fl = np.array(exit_flags_box(c, box, x, y, h, "gm")).T
+        out = alive & fl.any(axis=1)
+        K[out] = n
+        flags[out] = fl[out]
+        alive &= ~out
+    d = np.stack([abs(x - box[1]), abs(y - box[3]), abs(x - box[0]), abs(y - box[2])], axis=1)
+    d = np.sort(np.where(flags, d, np.inf), axis=1)
+    clear &= d[:, 1] - d[:, 0] > 3e-4
+    rec = dict(x=x, y=y, Y=Y, Z=Z, flags=flags, K=K)
+    return K, X, YZ, path_scores(g, c, k, rec, c.exact(g.x, g.y)), clear
+
+
+@pytest.mark.parametrize("kind,paths,points", [("varcoef", 40, 21), ("lut", 33, 70), ("poisson", 65, 9)])
+def test_collected_points_follow_the_paths(ctx, kind, paths, points):
+    """Every recorded point and target of a dozen knots against the paths walked in
+    float64 (drift, reaction and an off-diagonal sigma among them; odd and even steps,
+    several chunks of eight, points to the end of a path).  A step is about 0.05 wide and
+    float32 leaves some 1e-6 of it: 1e-4 on the points.  A target's error is that of the
+    points times the gradients of the source over the path's time and of the exit value
+    (below 50) from points within 2e-5: 1e-3, where one step's Z or Y makes 4e-3 or more."""
+    w = dict(kind=kind, param=(), domain=(0.0, 1.0, 0.0, 1.0), H=3, m=5, ext=2, n_paths=paths, h=2e-3, seed=9,
+             precision="fp32", exit_rule="gm")
+    tab = lut = None
+    if kind == "lut":
+        w["lut_n"] = 33
+        tab = workloads.varied_lut(33)
+        lut = torch.from_numpy(tab).cuda()
+    g = Geometry(w["domain"], w["H"], w["m"], w["ext"])
+    c = Coefficients(kind, (), lut=tab, lut_n=w.get("lut_n", 0), domain=w["domain"])
+    u0 = torch.from_numpy(c.exact(g.x, g.y)).cuda()
+    xy, t = ctx.collect(w, u0, paths, points, lut=lut)
+    ctx.sync()
+    xy = xy.cpu().numpy().reshape(g.n, paths, points, 2)
+    t = t.cpu().numpy().reshape(g.n, paths, points)
+    compared = 0
+    for k in range(0, g.n, 4):
+        K, X, YZ, v, clear = _walk(g, c, k, paths, w, points)
+        used = np.arange(points)[None, :] < np.minimum(K, points)[:, None]
+        assert np.array_equal(np.isfinite(t[k])[clear], used[clear]), k
+        sel = used & clear[:, None]
+        want = (v[:, None] - YZ[:, :, 1]) / YZ[:, :, 0]
+        assert np.abs(xy[k] - X)[sel].max() <= 1e-4, k
+        assert (np.abs(t[k] - want)[sel] <= 1e-3 * (1.0 + np.abs(want[sel]))).all(), k
+        compared += sel.sum()
+    assert compared > 13 * paths * min(points, 8) // 2
