@@ -363,7 +363,8 @@ pdd_status pdd_solve_noalloc(pdd_ctx* ctx, int64_t n, const int32_t* row_ptr, co
  * point), h; cv, n_paths_per_knot and dump must be unset and interp must be
  * PDD_INTERP_HAT (else PDD_EUNSUPPORTED).  Path p of point i
  * draws from the Philox counter (draw, p, i, instance + 2^31), disjoint from
- * the knot streams of assemblies with instance < 2^31. */
+ * the knot streams of assemblies with instance < 2^31.  The scores are added in
+ * float64 in a fixed order, which a captured call may take differently. */
 pdd_status pdd_eval_subdomain(pdd_ctx* ctx, const pdd_coeffs* coeffs, const pdd_partition* part,
                               const pdd_knots* knots, const double* u_knots, int64_t n_pts, const double* xy,
                               const pdd_run* run, double* u, double* se);

@@ -113,7 +113,8 @@ __device__ R exit_value(const AsmParams& P, const KnotDesc& d, const double* u0,
 // 300 G/s, VALU busy 62 %), hence the cells below; without one, VALU issue and the
 // longest paths.  11,241 knots x 1000 paths of 421 steps (EQ43, table, RBF weights):
 // 51.9 ms with every exit kept in its lane until 16 waited, 45.8 with the queue,
-// 38.2 with the cells.  POISSON, 2000 paths of hat weights a knot: 2.54 and 1.29.
+// 38.2 with the cells, with half the requests to L2 and VALU busy 85 %: VALU issue
+// bounds that form.  POISSON, 2000 paths of hat weights a knot: 2.54 and 1.29.
 // REFILL 4, 8, 16: 46.3, 45.4, 45.8 there, and 1.00, 0.98, 0.93 ms for 209 paths a
 // knot, where starting a path (its thresholds in float64) counts.
 constexpr int REFILL = 16;

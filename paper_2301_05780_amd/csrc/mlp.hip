@@ -152,8 +152,8 @@ __global__ __launch_bounds__(BLK) void k_mlp_bake(const float* __restrict__ para
 // the update.  Per step (us; one workgroup for the batch, and above 1024 one launch
 // for the slices' gradients and one for Adam, against this form):
 //   batch      32    100    256   1024   4096   20,000   65,537
-//   before   21.6   20.0   31.5    111    117      399     1203
-//   now      15.0   15.7   15.4     44     32       84      182
+//   before   18.3   18.6   31.5    109    109      366     1163
+//   now      10.7   13.0   14.1     37     21       48      112
 // With shares of the parameters and two exchanges a single slice took 17.1 for 256.
 //
 // Eight waves per workgroup, two rounds (tiles of 32 points) at a time, points as

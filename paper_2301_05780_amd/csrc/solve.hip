@@ -233,8 +233,8 @@ __global__ void k_zero_words(int32_t* w, int32_t count) {
 
 // ---- the whole solve in one launch ------------------------------------------
 // Bound by latency: a system of a few thousand unknowns is a chain of some
-// sixty iterations with two products and four reductions each, and as ten
-// launches an iteration it took 43 us (1729 unknowns, 60 iterations: 2.6 ms;
+// forty iterations with two products and three reductions each, and as ten
+// launches an iteration it took 60 us (1729 unknowns, 40 to 44 iterations: 2.6 ms;
 // now 0.79 ms; 29 unknowns 0.57 ms, now 0.085; 15,105 5.9 ms, now 3.2).
 // Here G workgroups (at most one per CU) each own a contiguous range of rows
 // and keep the whole vectors r, p, v redundantly in registers (thread t
