@@ -269,8 +269,8 @@ inline int64_t solo_ticket(int64_t paths, int64_t waves) {
 // lane) and no more than 1.7 tickets per wave.  29 knots of 1000 float64 paths:
 // 1.02 ms with 256, 0.64 ms with 64; 369 knots of 1000: 0.92, 0.69 ms; 369 of 4000:
 // 1.20, 0.99 ms; 1729 of 1000: 2.01, 1.82 ms.
-// Over 238 runs (10 geometries, 8 to 100 steps, equal and unequal counts) 256 over this
-// cut: 0.88 to 1.51, 1.05 to 1.2 on average from 1.25 tickets of 256 per wave down to 0.15.
+// 256 over this cut, means of four seeds at 110 random sizes (6 to 100 steps): 0.98 to
+// 1.5; 1.14 on average below half a ticket of 256 per wave, 1.06 up to one, 1.03 above.
 //   Large runs: per_wave tickets' worth of paths per wave; shorter tickets than 256 cost
 // more.  No other number of them is better in general: of 1729 knots of 10,000 paths the
 // times for 4.5 to 8.7 tickets per wave lie between 1.03 ms (5.63) and 1.16 (5.91, 8.16),
