@@ -83,7 +83,7 @@ pdd_status run_assemble_batch(pdd_ctx* ctx, int32_t n, const pdd_instance* in) {
 
   // paths per knot of every instance (validated while building)
   std::vector<std::vector<int32_t>> npk(n);
-  int64_t total_paths = 0;
+  int64_t total_paths = 0, total_knots = 0;
   std::vector<int64_t> n_knots(n);
   for (int32_t i = 0; i < n; ++i) {
     // knot count without building the pattern
@@ -91,6 +91,7 @@ pdd_status run_assemble_batch(pdd_ctx* ctx, int32_t n, const pdd_instance* in) {
     if (H < 2 || m < 1) return bad(ctx, PDD_EINVAL, "pdd_assemble_batch: invalid partition");
     n_knots[i] = knot_count((int32_t)H, (int32_t)m);
     npk[i].resize(n_knots[i]);
+    total_knots += n_knots[i];
     for (int64_t k = 0; k < n_knots[i]; ++k) {
       const int64_t v = in[i].run.n_paths_per_knot ? in[i].run.n_paths_per_knot[k] : in[i].run.n_paths;
       if (v < 1 || v > INT32_MAX) return bad(ctx, PDD_EINVAL, "pdd_assemble_batch: path counts must be >= 1");
@@ -136,7 +137,7 @@ pdd_status run_assemble_batch(pdd_ctx* ctx, int32_t n, const pdd_instance* in) {
     solo = true;
     block = 64;
     if ((st = shape(slot_guess, blk, lds, grid)) != PDD_OK) return st;
-    if (!solo_pays(total_paths, grid, strided)) {
+    if (!solo_pays(total_paths, grid, strided, total_knots)) {
       solo = false;
       block = 256;
       if ((st = shape(slot_guess, blk, lds, grid)) != PDD_OK) return st;

@@ -242,16 +242,6 @@ inline bool default_shape(const pdd_ctx* ctx) {
   return !ctx->force_block && !ctx->force_grid && !ctx->force_per_ticket && ctx->spare_rows < 0 &&
          ctx->schedule == PDD_SCHEDULE_STATIC;
 }
-// From how many paths per wave on: a ticket's last paths run with idle lanes,
-// so a small run loses more than the balance gives, unless one row per wave
-// lets many more waves reside than two rows do (`waves` against `strided`).
-// Measured old / new time: equal residency 0.9 at 6750 paths per wave, 1.0 at
-// 8400; 1.25 times the waves 0.97 at 4700; 1.33 times 0.93 at 1480, 1.10 at
-// 5900, 1.35 at 74,000; 2.25 times 1.19 at 2430, 2.7 at 24,000.
-inline bool solo_pays(int64_t paths, int64_t waves, int64_t strided) {
-  const double r = (double)waves / (double)std::max<int64_t>(strided, 1);
-  return (double)paths >= std::max(2048.0, 16384.0 / (r * r * r * r)) * (double)waves;
-}
 // Paths per ticket: fewer cost more drained lanes (about 60 paths' worth per
 // ticket), more a longer wait for the last ticket: 8 sqrt(paths per wave) is
 // 2800 for the 4096^2 table (1250 to 2500: 30.3 ms; 5000: 34), 970 for the
@@ -259,6 +249,23 @@ inline bool solo_pays(int64_t paths, int64_t waves, int64_t strided) {
 // (4096: 76.9, 8192: 74.9, whole knots: 78.4 ms).
 inline int64_t solo_ticket(int64_t paths, int64_t waves) {
   return std::max<int64_t>(64, (int64_t)(8.0 * std::sqrt((double)paths / (double)std::max<int64_t>(waves, 1))));
+}
+// From how many paths per wave on: a ticket's last paths run with idle lanes,
+// so a small run loses more than the balance gives, unless one row per wave
+// lets many more waves reside than two rows do (`waves` against `strided`).
+// Measured old / new time: equal residency 0.9 at 6750 paths per wave, 1.0 at
+// 8400; 1.25 times the waves 0.97 at 4700; 1.33 times 0.93 at 1480, 1.10 at
+// 5900, 1.35 at 74,000; 2.25 times 1.19 at 2430, 2.7 at 24,000.
+// No ticket is longer than a knot's paths (`knots` of them), and short ones lose
+// their lanes' ends more often: with 1.67 times the waves and 2700 paths per wave
+// 0.82 at 213 paths per knot, 1.03 at 349 (a table with 34,753 knots 0.92 at 450), with
+// 6000 per wave 1.03 at 214, with 9000 1.17 at 321; with 2.12 times the waves 0.90 at
+// 67 (2100 per wave), 0.97 at 112 (3500), 1.15 at 168 (2700).
+inline bool solo_pays(int64_t paths, int64_t waves, int64_t strided, int64_t knots) {
+  const double r = (double)waves / (double)std::max<int64_t>(strided, 1), r4 = r * r * r * r;
+  const double per_wave = (double)paths / (double)std::max<int64_t>(waves, 1);
+  const double ticket = std::min((double)solo_ticket(paths, waves), (double)paths / (double)std::max<int64_t>(knots, 1));
+  return per_wave >= std::max(2048.0, 16384.0 / r4) && ticket * per_wave >= 1.1e7 / r4;
 }
 
 // Paths per ticket under the fixed stride.  `paths` in all on `waves` waves;

@@ -268,7 +268,7 @@ pdd_status run_assemble(pdd_ctx* ctx, const AssembleJob& job) {
                                 lane_kernel)) != hipSuccess)
       return check_hip(ctx, e, "occupancy query");
     const int64_t solo_grid = (int64_t)ctx->cu_count * std::max(per_cu, 1);
-    solo = solo_pays(total, solo_grid, grid * (block / 64));
+    solo = solo_pays(total, solo_grid, grid * (block / 64), g.n);
     if (solo) {
       block = 64;
       lds = one;
