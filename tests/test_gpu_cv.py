@@ -730,3 +730,42 @@ def test_collected_points_follow_the_paths(ctx, kind, paths, points):
         assert (np.abs(t[k] - want)[sel] <= 1e-3 * (1.0 + np.abs(want[sel]))).all(), k
         compared += sel.sum()
     assert compared > 13 * paths * min(points, 8) // 2
+
+
+@pytest.mark.parametrize("polls", [-1, 500])
+def test_training_beside_a_long_assembly(ctx, polls):
+    """A batch's training on one stream while an assembly of another context fills the
+    device on a second one: the bits of the call alone, whether its workgroups wait
+    for the assembly or the first one gives the others up."""
+    steps, batch, lr = 4, 1300, 1e-3
+    rng = np.random.default_rng(23)
+    X, T = _dev(rng.uniform(0, 1, size=(batch, 2)), np.float32), _dev(rng.normal(size=batch), np.float32)
+    order = _dev(workloads.minibatch_order(batch, 4, seed=6), np.int32)
+
+    def train():
+        p = _dev(_theta(7, noise=0.0), np.float32)
+        m, s = torch.zeros_like(p), torch.zeros_like(p)
+        torch.cuda.current_stream().synchronize()
+        losses = ctx.mlp_train(p, m, s, X, T, order, batch, steps, 0, lr)
+        return p, m, s, losses
+
+    own = train()
+    other, streams = pdd.Context(0), [torch.cuda.Stream(), torch.cuda.Stream()]
+    long = dict(workloads.varcoef(), n_paths=200000)
+    try:
+        out = other.assemble(long)
+        torch.cuda.synchronize()
+        other.check(pdd.lib().pdd_set_stream(other.h, streams[0].cuda_stream))
+        ctx.check(pdd.lib().pdd_set_stream(ctx.h, streams[1].cuda_stream))
+        ctx.set_wait_limit(polls)
+        for _ in range(3):
+            other.assemble(long, out=out)
+            got = train()
+            torch.cuda.synchronize()
+            for a, b in zip(got, own):
+                assert torch.equal(a, b)
+    finally:
+        torch.cuda.synchronize()
+        ctx.set_wait_limit()
+        ctx.check(pdd.lib().pdd_set_stream(ctx.h, ctx.stream.cuda_stream))
+        other.close()
